@@ -481,13 +481,13 @@ int dc_set_multi_tile_mode(int32_t mode);
 
 /* Kernel form of the reduced operator S = D_ee - D_eo D_oo^{-1} D_oe (Sec. 2.2,
  * factored form) in dc_apply_reduced, dc_apply_reduced_bj and the reduced
- * solves; process-wide.  mode 0 (default): for FP32 and FP16 blocks with n a
- * multiple of 8 (n <= 64), one kernel over the odd rows reads every hop block
- * once, forms D_oo^{-1} D_oe in and from the same read the D_eo products, and a
- * second kernel sums those per even row (ten blocks read per even/odd site
- * pair); FP64 and other n use the two-kernel form.  mode 1: always the
- * two-kernel form (each kernel reads the hop blocks of its rows: eighteen
- * blocks per pair).  The two forms add the same terms in the same order, so
+ * solves; process-wide.  mode 0 (default): for FP32 and FP16 blocks, and for
+ * FP64 blocks with n <= 48 of more than 24 MB in total, one kernel over the odd
+ * rows reads every hop block once, forms D_oo^{-1} D_oe in and from the same read
+ * the D_eo products, and a second kernel sums those per even row (ten blocks
+ * read per even/odd site pair); other FP64 operators use the two-kernel form.
+ * mode 1: always the two-kernel form (each kernel reads the hop blocks of its
+ * rows: eighteen blocks per pair).  The two forms add the same terms in the same order, so
  * results are equal bit for bit.  Other values: DC_ERR_INVALID.  Set it while
  * no call of the library runs on another thread. */
 int dc_set_reduced_kernels(int32_t mode);

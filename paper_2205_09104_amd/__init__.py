@@ -426,8 +426,8 @@ def set_multi_tile_mode(mode: int):
 
 def set_reduced_kernels(mode: int):
     """Reduced operator's kernel form (process-wide): 0 the single-read pair
-    where it applies (FP32 / FP16 blocks, n a multiple of 8), 1 always the
-    two-kernel form; equal results."""
+    where it applies (FP32 / FP16 blocks, FP64 blocks beyond 24 MB with n <= 48),
+    1 always the two-kernel form; equal results."""
     check(load().dc_set_reduced_kernels(int(mode)))
 
 

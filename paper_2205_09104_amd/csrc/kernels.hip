@@ -364,10 +364,26 @@ constexpr int kSlots = 9;
 // word) and are widened inside the mixed-precision FMAs.
 template <int T, int P>
 struct TileRegs {
-  cx<typename Tile<T, P>::A> m[T * T];
+  using A = typename Tile<T, P>::A;
+  static constexpr int TT = T * T;
+  static constexpr int UNITS = Tile<T, P>::UNITS;
+  cx<A> m[TT];
   __device__ void load(const void* base, int lane) { Tile<T, P>::load(base, lane, m); }
-  __device__ void load_stream(const void* base, int lane) { load(base, lane); }
-  __device__ float re(int e) const { return m[e].re; }
+  // the same with non-temporal loads, for tiles that one launch reads once
+  __device__ void load_stream(const void* base, int lane) {
+    typedef A avec __attribute__((ext_vector_type(16 / sizeof(A))));
+    const avec* p = static_cast<const avec*>(base);
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+      const avec v = __builtin_nontemporal_load(p + u * 64 + lane);
+      if constexpr (P == P64) {
+        m[u] = mk(v.x, v.y);
+      } else {
+        m[2 * u] = mk(v.x, v.y);
+        if (2 * u + 1 < TT) m[2 * u + 1] = mk(v.z, v.w);
+      }
+    }
+  }
 };
 
 template <int T>
@@ -923,11 +939,16 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduced_eo(
 // that lane (w, lc) forms for row a there, and the same row reduction over lc
 // finishes it.  FP16 tiles up to n = 48 fit three workgroups per CU (7 waves
 // per SIMD, 70 registers, no spill); at 8 waves per SIMD the registers spill
-// and the kernel runs slower.
+// and the kernel runs slower.  FP64 tiles of n = 48 take 202 registers, one
+// workgroup per CU: its 330 KB of loads are all in flight at once, so the CUs
+// that wait on loads keep HBM busy while others multiply.  HBM bound: 12^4,
+// n = 48, one apply with the gather: FP64 1179 us (two-kernel form) -> 752 us,
+// 5.1 TB/s of algorithmic bytes; FP32 580 -> 340 us, 5.6 TB/s; ragged n = 42,
+// FP64: 1605 -> 762 us.
 template <int T, int P>
 constexpr int scatter_min_waves() { return (P == P16S && T <= 6) ? 7 : 1; }
 
-template <int T, int P>
+template <int T, int P, bool FULL>
 __global__ __launch_bounds__(512, (scatter_min_waves<T, P>())) void k_reduced_scatter(
     const void* __restrict__ blocks, const float* __restrict__ scales,
     const void* __restrict__ inv, const float* __restrict__ invsc,
@@ -963,7 +984,7 @@ __global__ __launch_bounds__(512, (scatter_min_waves<T, P>())) void k_reduced_sc
     R.load_stream(block_ptr<T, P>(blocks, size_t(item)), lane);
     if (P == P16S) s = A(scales[item]);
     const int src = nbr[w * V + x];
-    wave_product<T, P, true, 1>(R, s, x_e + size_t(src >> 1) * n, part[w], n, 0.0, lane);
+    wave_product<T, P, FULL, 1>(R, s, x_e + size_t(src >> 1) * n, part[w], n, 0.0, lane);
     dst = (size_t(src >> 1) * 8 + 4 + w) * n;        // backward hop mu = w of even x + mu
   } else {
     const int mu = w - 4;
@@ -971,7 +992,7 @@ __global__ __launch_bounds__(512, (scatter_min_waves<T, P>())) void k_reduced_sc
     const int item = 5 * y + 1 + mu;
     R.load_stream(block_ptr<T, P>(blocks, size_t(item)), lane);
     if (P == P16S) s = A(scales[item]);
-    wave_product<T, P, true, 2>(R, s, x_e + size_t(y >> 1) * n, part[w], n, 0.0, lane);
+    wave_product<T, P, FULL, 2>(R, s, x_e + size_t(y >> 1) * n, part[w], n, 0.0, lane);
     dst = (size_t(y >> 1) * 8 + mu) * n;             // forward hop mu of even x - mu
   }
   __syncthreads();
@@ -1007,6 +1028,10 @@ __global__ __launch_bounds__(512, (scatter_min_waves<T, P>())) void k_reduced_sc
           const uint32_t word = (e & 3) == 0 ? q.x : (e & 3) == 1 ? q.y : (e & 3) == 2 ? q.z : q.w;
           zr = lo_h(word);
           zi = hi_h(word);
+        } else if constexpr (P == P64) {
+          const double2 q = reinterpret_cast<const double2*>(inv_lds)[e * 64 + src_lane];
+          zr = q.x;
+          zi = q.y;
         } else {
           const float4 q = reinterpret_cast<const float4*>(inv_lds)[(e >> 1) * 64 + src_lane];
           zr = (e & 1) ? q.z : q.x;
@@ -1025,9 +1050,9 @@ __global__ __launch_bounds__(512, (scatter_min_waves<T, P>())) void k_reduced_sc
   }
   __syncthreads();
   if (w < 4)
-    wave_product<T, P, true, 2>(R, s, tx, hp + dst, n, 0.0, lane);
+    wave_product<T, P, FULL, 2>(R, s, tx, hp + dst, n, 0.0, lane);
   else
-    wave_product<T, P, true, 1>(R, s, tx, hp + dst, n, 0.0, lane);
+    wave_product<T, P, FULL, 1>(R, s, tx, hp + dst, n, 0.0, lane);
 }
 
 // Second kernel of the single-read form: one wave per even row r (site
@@ -1035,7 +1060,7 @@ __global__ __launch_bounds__(512, (scatter_min_waves<T, P>())) void k_reduced_sc
 // are the hop terms k_reduced_eo sums from its own products; the row is then
 // finished as there: BJ x_e + A_e^{-1} (sum), else A_e x_e (+ i tm Gamma5 x_e)
 // with the terms added one by one, and the epilogue.
-template <int T, int P, int EPI, bool BJ>
+template <int T, int P, bool FULL, int EPI, bool BJ>
 __global__ __launch_bounds__(64) void k_reduced_gather(
     const void* __restrict__ blocks, const float* __restrict__ scales,
     const void* __restrict__ einv, const float* __restrict__ einvsc,
@@ -1092,7 +1117,7 @@ __global__ __launch_bounds__(64) void k_reduced_gather(
       if (q == lc) mine = mk(fr, fi);
     }
     const int row = lr * T + lc;
-    if (lc >= T) return;
+    if (lc >= T || !(FULL || row < n)) return;
     const size_t i = size_t(r) * n + row;
     cx<VR> o = mk(VR(mine.re), VR(mine.im));
     if (x_e) {
@@ -1106,7 +1131,7 @@ __global__ __launch_bounds__(64) void k_reduced_gather(
       const int item = 5 * x;
       R.load_stream(block_ptr<T, P>(blocks, size_t(item)), lane);
       const A s = (P == P16S) ? A(scales[item]) : A(1);
-      wave_product<T, P, true, 0>(R, s, x_e + size_t(r) * n, self_part, n, tm, lane);
+      wave_product<T, P, FULL, 0>(R, s, x_e + size_t(r) * n, self_part, n, tm, lane);
     } else {
       self_part[lane] = mk(VR(0), VR(0));
     }
@@ -3052,8 +3077,26 @@ void set_reduced_mode(int mode) {
 
 int reduced_mode() { return g_reduced_mode; }
 
-bool reduced_single_read(Prec p, int n) {
-  return g_reduced_mode != 1 && p != P64 && n % 8 == 0 && n >= 8 && n <= 64;
+// Tiles the single-read form takes: an FP64 tile of T >= 7 (n > 48) would not
+// fit the registers of its wave (2 T^2 doubles of 256 VGPRs at eight waves).
+template <int P>
+constexpr bool single_read_tile(int T) { return T >= 1 && T <= (P == P64 ? 6 : 8); }
+
+static bool single_read_fits(Prec p, int n) {
+  const int T = tile_T(n);
+  return p == P64 ? single_read_tile<P64>(T) : single_read_tile<P32>(T);
+}
+
+// FP64 operators whose blocks stay in the XCDs' L2 (8 x 4 MB) keep the
+// two-kernel form: its second read of a hop block is an L2 hit there and its
+// workgroups have one barrier instead of three.  Measured (whole FP64 solves,
+// two-kernel / single-read): 21 MB of blocks 9.47 / 9.72 ms, 26 MB 13.1 / 12.2,
+// 47 MB 14.1 / 12.6; one apply at 12^4, n = 48 (3.8 GB): 1179 / 752 us.
+constexpr size_t kSingleReadF64Bytes = size_t(24) << 20;
+
+bool reduced_single_read(Prec p, int n, int V) {
+  if (g_reduced_mode == 1 || !single_read_fits(p, n)) return false;
+  return p != P64 || size_t(V) * 5 * n * n * sizeof(z64) > kSingleReadF64Bytes;
 }
 
 template <int P>
@@ -3067,16 +3110,25 @@ static void reduced_scatter_T(int n, int V, const void* blocks, const float* sca
   const dim3 grid(unsigned(chunk) * 8u), block(512);
   const auto* xe = static_cast<const cx<VR>*>(x_e);
   auto* h = static_cast<cx<VR>*>(hp);
-  switch (n / 8) {
-#define DC_CASE(TV)                                                                          \
-  case TV:                                                                                   \
-    hipExtLaunchKernelGGL((k_reduced_scatter<TV, P>), grid, block, 0, st, ev0, ev1, 0, blocks, \
-                          scales, inv, invsc, xe, h, nbr, osite, V, n, chunk, done);         \
+  const bool full = (n % 8) == 0;
+  switch (tile_T(n)) {
+#define DC_CASE(TV)                                                                            \
+  case TV:                                                                                     \
+    if constexpr (single_read_tile<P>(TV)) {                                                   \
+      if (full)                                                                                \
+        hipExtLaunchKernelGGL((k_reduced_scatter<TV, P, true>), grid, block, 0, st, ev0, ev1,  \
+                              0, blocks, scales, inv, invsc, xe, h, nbr, osite, V, n, chunk,   \
+                              done);                                                           \
+      else                                                                                     \
+        hipExtLaunchKernelGGL((k_reduced_scatter<TV, P, false>), grid, block, 0, st, ev0, ev1, \
+                              0, blocks, scales, inv, invsc, xe, h, nbr, osite, V, n, chunk,   \
+                              done);                                                           \
+    }                                                                                          \
     break;
     DC_CASE(1) DC_CASE(2) DC_CASE(3) DC_CASE(4) DC_CASE(5) DC_CASE(6) DC_CASE(7) DC_CASE(8)
 #undef DC_CASE
     default:
-      throw InvalidArg("the single-read reduced kernels need n = 8, 16, ..., 64");
+      throw InvalidArg("block size n > 64 is not supported");
   }
   DC_HIP(hipGetLastError());
 }
@@ -3086,11 +3138,12 @@ void launch_reduced_scatter(Prec p, int n, int V, const void* blocks, const floa
                             const int* nbr, const int* osite, const int* done, hipStream_t st,
                             hipEvent_t ev0, hipEvent_t ev1) {
   if (V < 2 || V % 2) throw InvalidArg("the reduced operator needs an even number of sites");
-  if (p == P64 || n % 8 || n < 8 || n > 64)
-    throw InvalidArg("the single-read reduced kernels take FP32 / FP16 blocks with n = 8, ..., 64");
+  if (!single_read_fits(p, n))
+    throw InvalidArg("the single-read reduced kernels do not take this precision and block size");
   if (p == P16S && (!scales || !invsc)) throw InvalidArg("FP16 blocks need their scales");
   if (!x_e || !hp || !inv) throw InvalidArg("null pointer");
-  if (p == P32) reduced_scatter_T<P32>(n, V, blocks, scales, inv, invsc, x_e, hp, nbr, osite, done, st, ev0, ev1);
+  if (p == P64) reduced_scatter_T<P64>(n, V, blocks, scales, inv, invsc, x_e, hp, nbr, osite, done, st, ev0, ev1);
+  else if (p == P32) reduced_scatter_T<P32>(n, V, blocks, scales, inv, invsc, x_e, hp, nbr, osite, done, st, ev0, ev1);
   else reduced_scatter_T<P16S>(n, V, blocks, scales, inv, invsc, x_e, hp, nbr, osite, done, st, ev0, ev1);
 }
 
@@ -3109,17 +3162,25 @@ static void reduced_gather_T(int n, int V, const void* blocks, const float* scal
   auto* o = static_cast<cx<VR>*>(out);
   const auto* ee = static_cast<const cx<VR>*>(e);
   auto* yy = static_cast<cx<VR>*>(y);
-  switch (n / 8) {
-#define DC_CASE(TV)                                                                            \
-  case TV:                                                                                     \
-    hipExtLaunchKernelGGL((k_reduced_gather<TV, P, EPI, BJ>), grid, block, 0, st, ev0, ev1, 0, \
-                          blocks, scales, einv, einvsc, xe, h, esite, V, n, chunk, tm, o, ee, yy, \
-                          c0, ca, cb, done);                                                   \
+  const bool full = (n % 8) == 0;
+  switch (tile_T(n)) {
+#define DC_CASE(TV)                                                                             \
+  case TV:                                                                                      \
+    if constexpr (single_read_tile<P>(TV)) {                                                    \
+      if (full)                                                                                 \
+        hipExtLaunchKernelGGL((k_reduced_gather<TV, P, true, EPI, BJ>), grid, block, 0, st,     \
+                              ev0, ev1, 0, blocks, scales, einv, einvsc, xe, h, esite, V, n,    \
+                              chunk, tm, o, ee, yy, c0, ca, cb, done);                          \
+      else                                                                                      \
+        hipExtLaunchKernelGGL((k_reduced_gather<TV, P, false, EPI, BJ>), grid, block, 0, st,    \
+                              ev0, ev1, 0, blocks, scales, einv, einvsc, xe, h, esite, V, n,    \
+                              chunk, tm, o, ee, yy, c0, ca, cb, done);                          \
+    }                                                                                           \
     break;
     DC_CASE(1) DC_CASE(2) DC_CASE(3) DC_CASE(4) DC_CASE(5) DC_CASE(6) DC_CASE(7) DC_CASE(8)
 #undef DC_CASE
     default:
-      throw InvalidArg("the single-read reduced kernels need n = 8, 16, ..., 64");
+      throw InvalidArg("block size n > 64 is not supported");
   }
   DC_HIP(hipGetLastError());
 }
@@ -3155,8 +3216,8 @@ void launch_reduced_gather(Prec p, int epi, int n, int V, const void* blocks,
                            const int* done, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   if (epi < 0 || epi > 3) throw InvalidArg("reduced epilogue must be 0..3");
   if (einv && epi == 3) throw InvalidArg("the residual epilogue takes the unpreconditioned operator");
-  if (p == P64 || n % 8 || n < 8 || n > 64)
-    throw InvalidArg("the single-read reduced kernels take FP32 / FP16 blocks with n = 8, ..., 64");
+  if (!single_read_fits(p, n))
+    throw InvalidArg("the single-read reduced kernels do not take this precision and block size");
   if (p == P16S && ((einv && !einvsc) || (!einv && !scales)))
     throw InvalidArg("FP16 blocks need their scales");
   if (V < 2 || V % 2) throw InvalidArg("the reduced operator needs an even number of sites");
@@ -3165,7 +3226,8 @@ void launch_reduced_gather(Prec p, int epi, int n, int V, const void* blocks,
   if ((epi == 1 || epi == 3) && !e) throw InvalidArg("null epilogue input");
   if ((epi == 1 || epi == 2) && !y) throw InvalidArg("null chain output");
 #define DC_ARGS epi, n, V, blocks, scales, einv, einvsc, x_e, hp, esite, tm, out, e, y, c0, ca, cb, done, st, ev0, ev1
-  if (p == P32) reduced_gather_P<P32>(DC_ARGS);
+  if (p == P64) reduced_gather_P<P64>(DC_ARGS);
+  else if (p == P32) reduced_gather_P<P32>(DC_ARGS);
   else reduced_gather_P<P16S>(DC_ARGS);
 #undef DC_ARGS
 }

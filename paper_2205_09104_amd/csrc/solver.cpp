@@ -644,7 +644,7 @@ void op_apply_reduced(Op& op, Prec p, int adjoint, int block_jacobi, const void*
     src = out;
   }
   const z64 z = mk(0.0, 0.0);
-  if (reduced_single_read(p, op.n)) {
+  if (reduced_single_read(p, op.n, op.V)) {
     void* hp = op.gbuf(p);
     reduced_scatter(op, p, inv, invsc, src, hp, nullptr, st);
     reduced_gather(op, p, 0, bj_e, bj_esc, src, hp, tm, out, nullptr, nullptr, z, z, z, nullptr,
@@ -932,7 +932,7 @@ struct Krylov {
   void reduced(const Z* in, int epi, Z* out, const Z* e, Z* y, z64 c0, z64 ca, z64 cb,
                const int* done) {
     const bool lbj = bjinv && epi != 3;
-    if (reduced_single_read(p, op.n)) {
+    if (reduced_single_read(p, op.n, op.V)) {
       reduced_scatter(op, p, oinv, oinvsc, in, gb, done, st);
       reduced_gather(op, p, epi, lbj ? bjinv : nullptr, lbj ? bjsc : nullptr, in, gb, tm, out, e,
                      y, c0, ca, cb, done, st);
