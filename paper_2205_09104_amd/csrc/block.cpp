@@ -207,13 +207,9 @@ struct BlockGmres {
       t[r + a] = out[a];
     }
     op.hs.write(tabs, t.data(), t.size() * sizeof(void*), st);
-    MultiOpDesc e{};
-    e.blocks = op.blocks(p);
-    e.scales = op.scales(p);
-    e.nbr = op.nbr.as<int>();
+    MultiOpDesc e = op.multi_desc(p);
     e.xin = const_cast<const void* const*>(tabs);
     e.yout = tabs + r;
-    e.V = op.V;
     e.R = r;
     e.tm = op.mu;
     launch_apply_multi_ops(p, op.n, &e, 1, 0, st);

@@ -1,6 +1,7 @@
 // HIP kernels for gfx950 (CDNA4): coarse-operator apply, Gram-Schmidt
 // reductions, tall-skinny combinations, conversions and the gradient kernel.
 #include "kernels.hpp"
+#include "device.hpp"
 
 #include <hip/hip_ext.h>
 
@@ -41,13 +42,6 @@ void* noalloc_scratch(bool setup) {
 }
 
 namespace {
-
-constexpr int kWave = 64;
-
-template <typename T>
-__device__ inline T shfl_xor(T v, int m) {
-  return __shfl_xor(v, m, kWave);
-}
 
 __device__ inline double gam(int i, int n) { return i < (n >> 1) ? 1.0 : -1.0; }
 
@@ -138,7 +132,8 @@ __device__ uint16_t f64_to_f16_rne(double x) {
 
 __global__ void k_layout(const z64* __restrict__ self_in, const z64* __restrict__ hops_in,
                          int V, int n, z64* __restrict__ o64, z32* __restrict__ o32,
-                         uint32_t* __restrict__ o16, float* __restrict__ sc16) {
+                         float* __restrict__ mx32, uint32_t* __restrict__ o16,
+                         float* __restrict__ sc16) {
   const int blk = blockIdx.x;  // site*5 + slot
   const int site = blk / 5, slot = blk % 5;
   const size_t nn = size_t(n) * n;
@@ -162,6 +157,7 @@ __global__ void k_layout(const z64* __restrict__ self_in, const z64* __restrict_
   const float scale = float(smax[0]);
   const double dscale = double(scale);
   if (o16 && threadIdx.x == 0) sc16[blk] = scale;
+  if (o32 && threadIdx.x == 0) mx32[blk] = scale;
   const int tt64 = ((TT + 0) / 1) * 1, tt32 = (TT + 1) / 2 * 2, tt16 = (TT + 3) / 4 * 4;
   const int total = 64 * tt16;  // covers every padded position of every layout
   for (int t = threadIdx.x; t < total; t += blockDim.x) {
@@ -416,13 +412,6 @@ struct TileRegs<T, P16S> {
     }
   }
 };
-
-__device__ inline float lo_h(uint32_t w) {
-  return float(__builtin_bit_cast(_Float16, static_cast<unsigned short>(w & 0xffffu)));
-}
-__device__ inline float hi_h(uint32_t w) {
-  return float(__builtin_bit_cast(_Float16, static_cast<unsigned short>(w >> 16)));
-}
 
 // Accumulate one lane's sub-tile: f_a += z_ac pc_c and (hop blocks)
 // g_c += conj(z_ac) pr_a.  npc_im = -Im(pc), npr_re = -Re(pr) avoid sign flips
@@ -1420,316 +1409,6 @@ __global__ void k_chain_groups(ChainGroups g, int first) {
                        static_cast<const cx<VR>* const*>(g.v[gi]),
                        static_cast<cx<VR>* const*>(g.prod[gi]), static_cast<cx<VR>* const*>(g.y[gi]),
                        g.N[gi], g.c0[gi], g.ca[gi], g.cb[gi], first, r);
-}
-
-// ------------------------------------------------------------------ multi-RHS apply
-// Y_r = D X_r for R right-hand sides at once.  One workgroup (4 waves) per
-// site accumulates the 9 couplings of the site into an n x R output panel
-// held in MFMA accumulators: each coupling stages its block (as the vector
-// precision) and the source panel in LDS, and the complex product runs as
-// three real GEMMs (Re M Re P, Im M Im P, (Re M + Im M)(Re P + Im P)) on
-// 16x16x4 MFMA tiles.
-// Backward hops Gamma5 B^H Gamma5 read the staged forward block transposed.
-// Every stored block is read once per site that uses it (9 block reads per
-// site; the MFMA work, 72 V n^2 R flops, dominates for R >= 16).
-template <typename VT>
-struct Mfma;
-template <>
-struct Mfma<float> {
-  using acc_t = __attribute__((ext_vector_type(4))) float;
-  __device__ static acc_t mma(float a, float b, acc_t c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-  __device__ static int row(int lk, int q) { return lk * 4 + q; }
-};
-template <>
-struct Mfma<double> {
-  using acc_t = __attribute__((ext_vector_type(4))) double;
-  __device__ static acc_t mma(double a, double b, acc_t c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  __device__ static int row(int lk, int q) { return lk + 4 * q; }
-};
-
-
-// The grid runs over a work list of the sites of up to kMaxMultiOps operators
-// (a mixed batch of lattices with one block size n): workgroup x belongs to the
-// operator whose site range [site0, site0 + V) contains it; grid.y tiles the
-// right-hand sides of the operator with the most, tiles past an operator's own
-// count exit at entry.
-template <int NP, int P, typename VT, int RB>
-__global__ __launch_bounds__(256) void k_apply_multi(MultiOps ops) {
-  static_assert(RB % 16 == 0 && RB <= 64, "right-hand-side tile of 16, 32 or 64");
-  using acc_t = typename Mfma<VT>::acc_t;
-  // select this workgroup's operator (uniform; fields copied by select so the
-  // kernel-argument array is never indexed dynamically)
-  int o = 0;
-#pragma unroll
-  for (int i = 1; i < kMaxMultiOps; ++i)
-    if (i < ops.n_ops && int(blockIdx.x) >= ops.op[i].site0) o = i;
-  const void* blocks = ops.op[0].blocks;
-  const float* scales = ops.op[0].scales;
-  const int* nbr = ops.op[0].nbr;
-  const void* const* xin_v = ops.op[0].xin;
-  void* const* yout_v = ops.op[0].yout;
-  int V = ops.op[0].V, R = ops.op[0].R, site0 = ops.op[0].site0;
-  double tm = ops.op[0].tm;
-#pragma unroll
-  for (int i = 1; i < kMaxMultiOps; ++i)
-    if (i == o) {
-      blocks = ops.op[i].blocks;
-      scales = ops.op[i].scales;
-      nbr = ops.op[i].nbr;
-      xin_v = ops.op[i].xin;
-      yout_v = ops.op[i].yout;
-      V = ops.op[i].V;
-      R = ops.op[i].R;
-      site0 = ops.op[i].site0;
-      tm = ops.op[i].tm;
-    }
-  const int n = ops.n, g5io = ops.g5io;
-  const auto* const* xin = reinterpret_cast<const cx<VT>* const*>(xin_v);
-  auto* const* yout = reinterpret_cast<cx<VT>* const*>(yout_v);
-  if (int(blockIdx.y) * RB >= R) return;
-  constexpr int LD = NP + 1;                  // padded row stride of every LDS plane
-  extern __shared__ unsigned char smem[];
-  VT* Mr = reinterpret_cast<VT*>(smem);       // [NP][LD] coupling matrix, real part
-  VT* Mi = Mr + NP * LD;                      // imaginary part
-  VT* Pr = Mi + NP * LD;                      // [RB][LD] panel: row r = x_r at the source
-  VT* Pi = Pr + RB * LD;
-  const int site = int(blockIdx.x) - site0;
-  const int r0 = blockIdx.y * RB;
-  const int Rc = min(RB, R - r0);
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int l16 = lane & 15, lk = lane >> 4;
-  const int T = (n + 7) / 8, TT = T * T;
-  constexpr int epl = (P == P64) ? 1 : (P == P32 ? 2 : 4);   // block entries per 16-byte unit
-  const int upl = (TT + epl - 1) / epl;                      // units per lane of a block
-  const int nunits = 64 * upl;
-  const int half = n >> 1;
-  // output tiles (16 x 16): RT row tiles x RB/16 column tiles; a partial
-  // right-hand-side tile computes on zero padding and stores only its Rc
-  // columns.  FP32 products: every wave gets the same share of MFMA work --
-  // the k range is split KS ways (KS = 4 / gcd(NT, 4)) and wave w takes k
-  // part w % KS of the TPW tiles (w / KS) TPW .. + TPW - 1 (3 row tiles x 1
-  // column tile, n = 48 with 16 right-hand sides, give each wave all 3 tiles
-  // over a quarter of k), the KS partial panels summed in LDS at the end.
-  // FP64 products keep one k range per tile (tile t = wave + 4 i): their
-  // wider accumulators would cost the occupancy the balance gains.
-  constexpr bool SPLIT = sizeof(VT) == 4;
-  constexpr int RT = NP / 16;
-  constexpr int NT = RT * (RB / 16);
-  constexpr int KS = !SPLIT ? 1 : ((NT % 4 == 0) ? 1 : ((NT % 2 == 0) ? 2 : 4));
-  constexpr int TPW = SPLIT ? NT * KS / 4 : (NT + 3) / 4;   // tiles per wave
-  constexpr int KSTEPS = NP / 4 / KS;   // 4-deep k steps per wave
-  static_assert((NP / 4) % KS == 0, "k range splits evenly");
-  const int kpart = wave % KS, tile0 = (wave / KS) * TPW;
-  auto tile_of = [&](int it) { return SPLIT ? tile0 + it : wave + 4 * it; };
-  // Staging with 16-byte loads.  Blocks: thread t takes units u = t + 256 s of
-  // the tiled block (lane u % 64, unit u / 64 of that lane), each holding epl
-  // entries whose (row, column) are fixed per thread and computed once.
-  // Panel: thread t takes 16-byte chunks c = t + 256 s (right-hand side c / CPR,
-  // chunk c % CPR of its n entries at the source site).
-  constexpr int TMAX = NP / 8;
-  constexpr int MU = (64 * ((TMAX * TMAX + epl - 1) / epl) + 255) / 256;
-  constexpr int VPC = 16 / int(sizeof(cx<VT>));             // vector entries per chunk
-  constexpr int CPRMAX = NP / VPC;
-  constexpr int PU = (RB * CPRMAX + 255) / 256;
-  const int cpr = n / VPC;                                   // chunks per right-hand side
-  int uoff[MU];                  // unit offset in the block (in 16-byte units), -1 if none
-  int ij[MU][epl];               // packed (row, column) of each entry, -1 if padding
-#pragma unroll
-  for (int s2 = 0; s2 < MU; ++s2) {
-    const int u = threadIdx.x + 256 * s2;
-    uoff[s2] = -1;
-#pragma unroll
-    for (int q = 0; q < epl; ++q) ij[s2][q] = -1;
-    if (u < nunits) {
-      const int l = u % 64, k = u / 64;
-      uoff[s2] = k * 64 + l;
-#pragma unroll
-      for (int q = 0; q < epl; ++q) {
-        const int e = k * epl + q;
-        if (e < TT) {
-          const int i = (l / 8) * T + e / T, j = (l % 8) * T + e % T;
-          if (i < n && j < n) ij[s2][q] = (i << 8) | j;
-        }
-      }
-    }
-  }
-  const cx<VT>* prow[PU];        // this thread's panel chunk sources (right-hand-side base)
-  int pr_[PU], pk_[PU];          // right-hand side and first component of each chunk
-#pragma unroll
-  for (int s2 = 0; s2 < PU; ++s2) {
-    const int c = threadIdx.x + 256 * s2;
-    const int r = c / cpr, k = (c % cpr) * VPC;
-    pr_[s2] = -1;
-    pk_[s2] = k;
-    prow[s2] = nullptr;
-    if (c < RB * cpr && r < Rc) {
-      pr_[s2] = r;
-      prow[s2] = xin[r0 + r];
-    }
-  }
-  // zero both planes once: padding rows / columns are never written again
-  for (int t = threadIdx.x; t < 2 * (NP + RB) * LD; t += blockDim.x) Mr[t] = VT(0);
-  __syncthreads();   // the zero fill must land before any staged value
-  // three real products per complex one: Re C = Mr Pr - Mi Pi,
-  // Im C = (Mr + Mi)(Pr + Pi) - Mr Pr - Mi Pi
-  acc_t crr[TPW], cii[TPW], css[TPW];
-#pragma unroll
-  for (int t = 0; t < TPW; ++t) {
-    crr[t] = acc_t{0, 0, 0, 0};
-    cii[t] = acc_t{0, 0, 0, 0};
-    css[t] = acc_t{0, 0, 0, 0};
-  }
-  uint4 mreg[MU], preg[PU];      // the next coupling's raw 16-byte units
-  int cblk = 0, csrc = 0;
-  float csc = 1.0f;
-  auto fetch = [&](int c, int& blk, int& src, float& sc) {
-    // coupling c: 0 self, 1..4 forward hop mu = c-1, 5..8 backward hop mu = c-5
-    if (c == 0) {
-      src = site;
-      blk = site * 5;
-    } else if (c < 5) {
-      src = nbr[(c - 1) * V + site];
-      blk = site * 5 + c;
-    } else {
-      src = nbr[(4 + c - 5) * V + site];       // x - mu
-      blk = src * 5 + (c - 4);                 // B[x-mu, mu]
-    }
-    sc = (P == P16S) ? scales[blk] : 1.0f;
-    const uint4* bu = reinterpret_cast<const uint4*>(blocks) + size_t(blk) * size_t(upl) * 64;
-#pragma unroll
-    for (int s2 = 0; s2 < MU; ++s2)
-      mreg[s2] = uoff[s2] >= 0 ? bu[uoff[s2]] : make_uint4(0, 0, 0, 0);
-#pragma unroll
-    for (int s2 = 0; s2 < PU; ++s2)
-      preg[s2] = pr_[s2] >= 0
-                     ? *reinterpret_cast<const uint4*>(prow[s2] + size_t(src) * n + pk_[s2])
-                     : make_uint4(0, 0, 0, 0);
-  };
-  fetch(0, cblk, csrc, csc);
-  for (int c = 0; c < 9; ++c) {
-    const bool trans = c >= 5;
-    const float sc = csc;
-    // raw units -> LDS planes (the previous coupling's products are done)
-#pragma unroll
-    for (int s2 = 0; s2 < MU; ++s2) {
-      const uint32_t w[4] = {mreg[s2].x, mreg[s2].y, mreg[s2].z, mreg[s2].w};
-#pragma unroll
-      for (int q = 0; q < epl; ++q) {
-        const int pij = ij[s2][q];
-        if (pij < 0) continue;
-        const int bi = pij >> 8, bj = pij & 255;
-        VT re, im;
-        if (P == P64) {
-          re = VT(__builtin_bit_cast(double, (uint64_t(w[1]) << 32) | w[0]));
-          im = VT(__builtin_bit_cast(double, (uint64_t(w[3]) << 32) | w[2]));
-        } else if (P == P32) {
-          re = VT(__builtin_bit_cast(float, w[2 * q]));
-          im = VT(__builtin_bit_cast(float, w[2 * q + 1]));
-        } else {
-          re = VT(lo_h(w[q]) * sc);
-          im = VT(hi_h(w[q]) * sc);
-        }
-        int i = bi, j = bj;
-        if (trans) {
-          // backward hop Gamma5 B^H Gamma5: M[i][j] = g_i g_j conj(B[j][i])
-          i = bj;
-          j = bi;
-          const VT sg = ((i < half) == (j < half)) ? VT(1) : VT(-1);
-          re = sg * re;
-          im = -sg * im;
-        }
-        if (c == 0 && i == j) im += VT(i < half ? tm : -tm);  // i * tm * Gamma5
-        Mr[i * LD + j] = re;
-        Mi[i * LD + j] = im;
-      }
-    }
-#pragma unroll
-    for (int s2 = 0; s2 < PU; ++s2) {
-      if (pr_[s2] < 0) continue;
-      const uint32_t w[4] = {preg[s2].x, preg[s2].y, preg[s2].z, preg[s2].w};
-      const int r = pr_[s2];
-#pragma unroll
-      for (int q = 0; q < VPC; ++q) {
-        const int k = pk_[s2] + q;
-        VT re, im;
-        if (sizeof(VT) == 8) {
-          re = VT(__builtin_bit_cast(double, (uint64_t(w[1]) << 32) | w[0]));
-          im = VT(__builtin_bit_cast(double, (uint64_t(w[3]) << 32) | w[2]));
-        } else {
-          re = VT(__builtin_bit_cast(float, w[2 * q]));
-          im = VT(__builtin_bit_cast(float, w[2 * q + 1]));
-        }
-        if ((g5io & 1) && k >= half) {
-          re = -re;
-          im = -im;
-        }
-        Pr[r * LD + k] = re;
-        Pi[r * LD + k] = im;
-      }
-    }
-    __syncthreads();
-    // the next coupling's loads are in flight while this one multiplies
-    if (c + 1 < 9) fetch(c + 1, cblk, csrc, csc);
-    // C += M P with the three products Mr Pr, Mi Pi, (Mr + Mi)(Pr + Pi)
-    // (16x16x4 tiles), k outermost so the wave's tiles interleave their MFMA
-    // chains
-#pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) {
-      const int k = 4 * (kpart * KSTEPS + ks);
-#pragma unroll
-      for (int it = 0; it < TPW; ++it) {
-        const int t = tile_of(it);
-        if (SPLIT || t < NT) {   // split tiles always exist
-          const int rt = t % RT, ct = t / RT;
-          const int ao = (rt * 16 + l16) * LD + lk + k, bo = (ct * 16 + l16) * LD + lk + k;
-          const VT a_r = Mr[ao], a_i = Mi[ao], b_r = Pr[bo], b_i = Pi[bo];
-          crr[it] = Mfma<VT>::mma(a_r, b_r, crr[it]);
-          cii[it] = Mfma<VT>::mma(a_i, b_i, cii[it]);
-          css[it] = Mfma<VT>::mma(a_r + a_i, b_r + b_i, css[it]);
-        }
-      }
-    }
-    __syncthreads();
-  }
-  // accumulators -> LDS panel planes (row r = right-hand side) -> coalesced
-  // stores; the k parts add their partial panels one after another
-#pragma unroll
-  for (int part = 0; part < KS; ++part) {
-    if (kpart == part) {
-#pragma unroll
-      for (int it = 0; it < TPW; ++it) {
-        const int t = tile_of(it);
-        if (!SPLIT && t >= NT) continue;
-        const int rt = t % RT, ct = t / RT;
-        const int col = ct * 16 + l16;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          // accumulator value q of a lane: row 4*(lane/16)+q for the FP32
-          // 16x16x4 MFMA, row lane/16 + 4*q for the FP64 one
-          const int row = rt * 16 + Mfma<VT>::row(lk, q);
-          const VT re = crr[it][q] - cii[it][q], im = css[it][q] - crr[it][q] - cii[it][q];
-          if (part == 0) {
-            Pr[col * LD + row] = re;
-            Pi[col * LD + row] = im;
-          } else {
-            Pr[col * LD + row] += re;
-            Pi[col * LD + row] += im;
-          }
-        }
-      }
-    }
-    __syncthreads();
-  }
-  for (int t = threadIdx.x; t < Rc * n; t += blockDim.x) {
-    const int r = t / n, i = t % n;
-    cx<VT> z = mk(Pr[r * LD + i], Pi[r * LD + i]);
-    if ((g5io & 2) && i >= half) z = mk(VT(-z.re), VT(-z.im));
-    yout[r0 + r][size_t(site) * n + i] = z;
-  }
 }
 
 template <typename VR>
@@ -2828,9 +2507,10 @@ inline unsigned grid_for(size_t N, int threads, unsigned cap = 4096) {
 // ====================================================================== launchers
 
 void launch_layout_blocks(const z64* self_in, const z64* hops_in, int V, int n, void* out64,
-                          void* out32, void* out16, float* scales16, hipStream_t st) {
+                          void* out32, float* max32, void* out16, float* scales16,
+                          hipStream_t st) {
   hipLaunchKernelGGL(k_layout, dim3(unsigned(V) * 5u), dim3(256), 0, st, self_in, hops_in, V, n,
-                     static_cast<z64*>(out64), static_cast<z32*>(out32),
+                     static_cast<z64*>(out64), static_cast<z32*>(out32), max32,
                      static_cast<uint32_t*>(out16), scales16);
   DC_HIP(hipGetLastError());
 }
@@ -3259,8 +2939,6 @@ void launch_bj_gather_poly(Prec p, int n, int V, const void* inv, const float* s
   bj_P<true, 2>(p, n, V, inv, scales, gbuf, prod, nullptr, y, z, ca, cb, done, st);
 }
 
-static int multi_np(int n) { return (n + 15) / 16 * 16; }
-
 void launch_chain_multi(Prec p, const void* const* t, const void* const* v, void* const* prod,
                         void* const* y, int R, size_t N, z64 c0, z64 ca, z64 cb, int first,
                         hipStream_t st) {
@@ -3295,150 +2973,6 @@ void launch_chain_groups(Prec p, const ChainGroups& g, int first, hipStream_t st
   if (p == P64) hipLaunchKernelGGL(k_chain_groups<double>, grid, block, 0, st, g, first);
   else hipLaunchKernelGGL(k_chain_groups<float>, grid, block, 0, st, g, first);
   DC_HIP(hipGetLastError());
-}
-
-size_t multi_lds_bytes(int n, bool dbl, int rb) {
-  const int np = multi_np(n);
-  return size_t(2) * (size_t(np) + rb) * (np + 1) * (dbl ? sizeof(double) : sizeof(float));
-}
-
-template <int NP, int P, typename VT, int RB>
-static void multi_launch(const MultiOps& ops, unsigned sites, int rmax, hipStream_t st) {
-  const size_t lds = multi_lds_bytes(ops.n, sizeof(VT) == 8, RB);
-  DC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_apply_multi<NP, P, VT, RB>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
-  const unsigned rtiles = unsigned((rmax + RB - 1) / RB);
-  hipLaunchKernelGGL((k_apply_multi<NP, P, VT, RB>), dim3(sites, rtiles), dim3(256), lds, st, ops);
-  DC_HIP(hipGetLastError());
-}
-
-template <int NP, typename VT, int P>
-static void multi_rb_launch(int rb, const MultiOps& ops, unsigned sites, int rmax, hipStream_t st) {
-  if (rb == 16) multi_launch<NP, P, VT, 16>(ops, sites, rmax, st);
-  else if (rb == 32 || sizeof(VT) == 8) multi_launch<NP, P, VT, 32>(ops, sites, rmax, st);
-  else multi_launch<NP, P, VT, (sizeof(VT) == 8 ? 32 : 64)>(ops, sites, rmax, st);
-}
-
-template <int NP>
-static void multi_np_launch(Prec p, int rb, const MultiOps& ops, unsigned sites, int rmax,
-                            hipStream_t st) {
-  if (p == P64) multi_rb_launch<NP, double, P64>(rb, ops, sites, rmax, st);
-  else if (p == P32) multi_rb_launch<NP, float, P32>(rb, ops, sites, rmax, st);
-  else multi_rb_launch<NP, float, P16S>(rb, ops, sites, rmax, st);
-}
-
-static void multi_dispatch(Prec p, int rb, const MultiOps& ops, unsigned sites, int rmax,
-                           hipStream_t st) {
-  switch (multi_np(ops.n)) {
-    case 16: multi_np_launch<16>(p, rb, ops, sites, rmax, st); break;
-    case 32: multi_np_launch<32>(p, rb, ops, sites, rmax, st); break;
-    case 48: multi_np_launch<48>(p, rb, ops, sites, rmax, st); break;
-    case 64: multi_np_launch<64>(p, rb, ops, sites, rmax, st); break;
-    default: throw InvalidArg("block size n > 64 is not supported");
-  }
-}
-
-// Autotuned right-hand-side tile (16, 32 or 64 per workgroup): the first launch
-// of a shape class (block size, precision, right-hand-side and site-count
-// buckets) times each candidate on the actual operands with HIP events and
-// keeps the fastest; later launches of the class use it.
-namespace {
-struct TuneKey {
-  int np, prec, rbucket, vbucket;
-  bool operator<(const TuneKey& o) const {
-    return std::tie(np, prec, rbucket, vbucket) < std::tie(o.np, o.prec, o.rbucket, o.vbucket);
-  }
-};
-std::mutex g_tune_mu;
-std::map<TuneKey, int> g_tune;
-int g_tune_mode = 0;  // 0: autotune; 16/32/64: forced tile
-
-TuneKey tune_key(Prec p, int n, int rmax, unsigned sites) {
-  int rbk = 0;
-  while ((16 << rbk) < rmax && rbk < 3) ++rbk;   // <=16, <=32, <=64, >64
-  int vb = 0;
-  while ((1u << (vb + 1)) <= sites && vb < 30) ++vb;  // floor(log2(sites))
-  return TuneKey{multi_np(n), int(p), rbk, vb};
-}
-}  // namespace
-
-int multi_tile_for(Prec p, int n, int rmax, unsigned sites) {
-  std::lock_guard<std::mutex> lk(g_tune_mu);
-  if (g_tune_mode) return g_tune_mode;
-  const auto it = g_tune.find(tune_key(p, n, rmax, sites));
-  return it == g_tune.end() ? 0 : it->second;
-}
-
-void set_multi_tile_mode(int mode) {
-  if (mode != 0 && mode != 16 && mode != 32 && mode != 64)
-    throw InvalidArg("tile mode must be 0 (autotune), 16, 32 or 64");
-  std::lock_guard<std::mutex> lk(g_tune_mu);
-  g_tune_mode = mode;
-  if (mode == 0) g_tune.clear();
-}
-
-void launch_apply_multi_ops(Prec p, int n, const MultiOpDesc* desc, int n_ops, int g5io,
-                            hipStream_t st) {
-  if (n_ops < 1 || n_ops > kMaxMultiOps) throw InvalidArg("1..8 operators per multi-apply");
-  if (multi_np(n) > 64) throw InvalidArg("block size n > 64 is not supported");
-  MultiOps ops{};
-  ops.n_ops = n_ops;
-  ops.n = n;
-  ops.g5io = g5io;
-  unsigned sites = 0;
-  int rmax = 0;
-  for (int i = 0; i < n_ops; ++i) {
-    ops.op[i] = desc[i];
-    ops.op[i].site0 = int(sites);
-    sites += unsigned(desc[i].V);
-    rmax = std::max(rmax, desc[i].R);
-  }
-  if (rmax <= 0 || sites == 0) return;
-  int rb = multi_tile_for(p, n, rmax, sites);
-  if (rb == 0) {
-    // time every candidate (each fully overwrites the outputs)
-    hipEvent_t e0, e1;
-    DC_HIP(hipEventCreate(&e0));
-    DC_HIP(hipEventCreate(&e1));
-    float best = 1e30f;
-    for (int cand : {16, 32, 64}) {
-      if (cand > 16 && (cand / 2) >= rmax) break;   // wider tiles than the batch
-      if (cand == 64 && p == P64) break;            // FP64 accumulators of 64 would spill
-      multi_dispatch(p, cand, ops, sites, rmax, st);   // warm
-      DC_HIP(hipEventRecord(e0, st));
-      for (int rep = 0; rep < 3; ++rep) multi_dispatch(p, cand, ops, sites, rmax, st);
-      DC_HIP(hipEventRecord(e1, st));
-      DC_HIP(hipEventSynchronize(e1));
-      float ms = 0.f;
-      DC_HIP(hipEventElapsedTime(&ms, e0, e1));
-      if (ms < best) {
-        best = ms;
-        rb = cand;
-      }
-    }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
-    std::lock_guard<std::mutex> lk(g_tune_mu);
-    g_tune[tune_key(p, n, rmax, sites)] = rb;
-    // the outputs come from the chosen tile, as in every later call (the FP32
-    // tiles split their sums differently and agree only to rounding)
-  }
-  multi_dispatch(p, rb, ops, sites, rmax, st);
-}
-
-void launch_apply_multi(Prec p, int n, int V, const void* blocks, const float* scales,
-                        const void* const* xin, void* const* yout, int R, const int* nbr, double tm,
-                        int g5io, hipStream_t st) {
-  MultiOpDesc d{};
-  d.blocks = blocks;
-  d.scales = scales;
-  d.nbr = nbr;
-  d.xin = xin;
-  d.yout = yout;
-  d.V = V;
-  d.R = R;
-  d.tm = tm;
-  launch_apply_multi_ops(p, n, &d, 1, g5io, st);
 }
 
 void launch_gather_store(Prec p, int n, int V, const void* gbuf, void* out, const int* done,

@@ -27,9 +27,10 @@ constexpr int kRedCap = 65536;
 
 // ---------------------------------------------------------------- operator
 // Re-lay out FP64 input blocks (self [V][n][n] + hops [V][4][n][n], device,
-// row-major) into the tiled per-lane layout of each requested precision.
+// row-major) into the tiled per-lane layout of each requested precision; max32
+// (with out32) and scales16 (with out16) take the largest |Re|, |Im| of each block.
 void launch_layout_blocks(const z64* self_in, const z64* hops_in, int V, int n,
-                          void* out64, void* out32, void* out16, float* scales16,
+                          void* out64, void* out32, float* max32, void* out16, float* scales16,
                           hipStream_t st);
 
 // Neighbour table int32 [8][V]: rows 0..3 = x + mu, rows 4..7 = x - mu.
@@ -138,9 +139,6 @@ void launch_oddeven_split(Prec p, int n, int half_sites, const int* esite, const
 // yout[r] = D xin[r] for r < R (device arrays of R vector pointers, vectors in
 // the precision's vector type), MFMA based; g5io bit 0 multiplies inputs and
 // bit 1 outputs by Gamma5 (adjoint through Gamma5 D(-mu) Gamma5 with tm = -mu).
-void launch_apply_multi(Prec p, int n, int V, const void* blocks, const float* scales,
-                        const void* const* xin, void* const* yout, int R, const int* nbr, double tm,
-                        int g5io, hipStream_t st);
 size_t multi_lds_bytes(int n, bool dbl, int rb);
 // right-hand-side tile chosen for a multi-apply shape (0: not tuned yet), and
 // the tuning mode (0: autotune, 16/32/64: force that tile; 0 clears the table)
@@ -152,11 +150,12 @@ void set_multi_tile_mode(int mode);
 constexpr int kMaxMultiOps = 8;
 struct MultiOpDesc {
   const void* blocks = nullptr;
-  const float* scales = nullptr;
+  const float* scales = nullptr;   // FP16: block scales; FP32: largest entry of each block
   const int* nbr = nullptr;
   const void* const* xin = nullptr;
   void* const* yout = nullptr;
   int V = 0, R = 0, site0 = 0;   // site0: set by the launcher
+  int dims[4] = {1, 1, 1, 1};    // lattice extents, product V
   double tm = 0.0;
 };
 struct MultiOps {

@@ -105,6 +105,7 @@ void Op::bind_arenas() {
   bind(nbr, P, "neighbour table");
   bind(blk64, P, "FP64 blocks");
   bind(blk32, P, "FP32 blocks");
+  bind(mx32, P, "FP32 block maxima");
   bind(blk16, P, "FP16 blocks");
   bind(sc16, P, "FP16 scales");
   for (auto& b : bj) {
@@ -182,8 +183,8 @@ static void copy_blocks_in(Op& op, const void* self_blocks, const void* hop_bloc
     dself = s;
     dhops = s + size_t(op.V) * nn;
   }
-  launch_layout_blocks(dself, dhops, op.V, op.n, op.blk64.p, op.blk32.p, op.blk16.p,
-                       op.sc16.as<float>(), st);
+  launch_layout_blocks(dself, dhops, op.V, op.n, op.blk64.p, op.blk32.p, op.mx32.as<float>(),
+                       op.blk16.p, op.sc16.as<float>(), st);
   DC_HIP(hipStreamSynchronize(st));
 }
 
@@ -207,7 +208,10 @@ void op_build(Op& op, const int dims[4], int n_tv, int store, double mu, const v
   launch_neighbours(op.nbr.as<int>(), dims[0], dims[1], dims[2], dims[3], st);
   const size_t nb = size_t(op.V) * 5;
   op.blk64.alloc(nb * block_units(op.n, P64) * 16);
-  if (op.store & 2) op.blk32.alloc(nb * block_units(op.n, P32) * 16);
+  if (op.store & 2) {
+    op.blk32.alloc(nb * block_units(op.n, P32) * 16);
+    op.mx32.alloc(nb * sizeof(float));
+  }
   if (op.store & 4) {
     op.blk16.alloc(nb * block_units(op.n, P16S) * 16);
     op.sc16.alloc(nb * sizeof(float));
@@ -726,8 +730,12 @@ void op_apply_multi(Op& op, Prec p, int adjoint, int R, const void* in, void* ou
   void** table = op.ptrs.as<void*>();
   const void* const* xin = const_cast<const void* const*>(table);
   void* const* yout = table + R;
-  launch_apply_multi(p, op.n, op.V, op.blocks(p), op.scales(p), xin, yout, R, op.nbr.as<int>(),
-                     adjoint ? -op.mu : op.mu, adjoint ? 3 : 0, st);
+  MultiOpDesc d = op.multi_desc(p);
+  d.xin = xin;
+  d.yout = yout;
+  d.R = R;
+  d.tm = adjoint ? -op.mu : op.mu;
+  launch_apply_multi_ops(p, op.n, &d, 1, adjoint ? 3 : 0, st);
 }
 
 // ============================================================================ Krylov
@@ -2114,13 +2122,9 @@ struct Batch {
     for (size_t gi = 0; gi < g.size(); ++gi) {
       const Group& gr = g[gi];
       if (gr.act.empty()) continue;
-      MultiOpDesc e{};
-      e.blocks = gr.op->blocks(pa);
-      e.scales = gr.op->scales(pa);
-      e.nbr = static_cast<const int*>(gr.op->nbr.p);
+      MultiOpDesc e = gr.op->multi_desc(pa);
       e.xin = reinterpret_cast<const void* const*>(slot(int(gi), in));
       e.yout = reinterpret_cast<void* const*>(slot(int(gi), out));
-      e.V = gr.op->V;
       e.R = int(gr.act.size());
       e.tm = gr.var->sign * gr.op->mu;
       d.push_back(e);
@@ -2724,12 +2728,9 @@ static int solve_groups(const std::vector<Op*>& ops, const SolveOpts& o, int adj
       std::vector<MultiOpDesc> d;
       for (size_t gi = 0; gi < G; ++gi) {
         if (act[gi].empty()) continue;
-        MultiOpDesc e{};
-        e.blocks = ops[gi]->blocks(P64);
-        e.nbr = ops[gi]->nbr.as<int>();
+        MultiOpDesc e = ops[gi]->multi_desc(P64);
         e.xin = const_cast<const void* const*>(tab.as<void*>() + off[gi]);
         e.yout = tab.as<void*>() + off[gi] + act[gi].size();
-        e.V = ops[gi]->V;
         e.R = int(act[gi].size());
         e.tm = vars[gi]->sign * ops[gi]->mu;
         d.push_back(e);
@@ -2865,7 +2866,7 @@ void workspace_bytes(const int dims[4], int n_tv, int store, double mu, bool hos
   const int nsign = mu != 0.0 ? 2 : 1;    // the adjoint's D(-mu) variant keeps its own state
   // persistent: tables, blocks, inverses, recycle spaces
   size_t P = R(8 * V * sizeof(int)) + R(5 * V * block_units(int(n), P64) * 16);
-  if (store & 2) P += R(5 * V * block_units(int(n), P32) * 16);
+  if (store & 2) P += R(5 * V * block_units(int(n), P32) * 16) + R(5 * V * sizeof(float));
   if (store & 4) P += R(5 * V * block_units(int(n), P16S) * 16) + R(5 * V * sizeof(float));
   if (oddeven) P += 2 * R(half * sizeof(int));
   if (build_persistent) *build_persistent = P;

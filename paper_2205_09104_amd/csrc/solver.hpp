@@ -234,7 +234,7 @@ struct Op {
   double mu = 0.0;
   long version = 0;     // bumped by update_coarse_op
   hipStream_t stream = nullptr;
-  DevBuf nbr, blk64, blk32, blk16, sc16;
+  DevBuf nbr, blk64, blk32, mx32, blk16, sc16;   // mx32: largest entry of each block
   struct BJ {                        // block-Jacobi inverses (tiled), per sign of mu
     DevBuf b64, b32, b16, sc16;
     long version = -1;
@@ -272,6 +272,18 @@ struct Op {
   Variant& variant(Prec p, int sign, int bj, int d, int schur = 0);
   const void* blocks(Prec p) const;
   const float* scales(Prec p) const { return p == P16S ? sc16.as<float>() : nullptr; }
+  // what the multi-right-hand-side apply scales the blocks by
+  const float* multi_scales(Prec p) const { return p == P32 ? mx32.as<float>() : scales(p); }
+  // this operator's entry of a multi-apply work list (xin, yout, R, tm: the caller's)
+  MultiOpDesc multi_desc(Prec p) const {
+    MultiOpDesc d{};
+    d.blocks = blocks(p);
+    d.scales = multi_scales(p);
+    d.nbr = nbr.as<int>();
+    d.V = V;
+    for (int i = 0; i < 4; ++i) d.dims[i] = dims[i];
+    return d;
+  }
   void* gbuf(Prec p) const { return p == P64 ? gbuf64.p : gbuf32.p; }
 };
 

@@ -39,3 +39,62 @@ def test_single_read_ragged_and_f64(dims, ntv, mu, precs):
             log(f"  {dims} n {oop.n} {prec} {kw}: max |difference| {float((a - b).abs().max()):.1e}")
             assert torch.equal(a, b) and bool(torch.isfinite(b.abs()).all())
     gop.close()
+
+
+def _rel(y, ref):
+    return float((y - ref).abs().norm() / ref.abs().norm())
+
+
+# Multi-right-hand-side apply on FP16 pieces: tiles T = 1..8 (full and ragged),
+# right-hand sides around the column tiles, extents that leave partial 4 x 4 x 4 bricks.
+# The bound is the one of the oracle comparison of these kernels (2e-6 of the same
+# storage's result), here against R single applies in the same storage.
+@pytest.mark.parametrize("dims,ntv,R", [((5, 3, 6, 2), 1, 1), ((4, 4, 4, 2), 4, 15),
+                                        ((6, 5, 1, 3), 7, 16), ((2, 7, 3, 2), 8, 17),
+                                        ((4, 1, 5, 2), 12, 33), ((3, 2, 2, 2), 15, 64),
+                                        ((2, 3, 2, 2), 20, 65), ((5, 2, 2, 1), 22, 32),
+                                        ((2, 2, 3, 2), 28, 31), ((2, 2, 2, 2), 32, 64)])
+def test_multi_pieces_tiles(dims, ntv, R):
+    import paper_2205_09104_amd as dc
+    gop, oop = make_pair(dims, ntv, 3.0, mu=0.2, store=("f64", "f32", "f16s"))
+    X = torch.stack([rand_vec(oop.V, oop.n, 23, r) for r in range(R)]).cuda().to(torch.complex64)
+    for prec in ("f32", "f16s"):
+        for adj in (False, True):
+            ref = torch.stack([gop.apply(x, prec=prec, adjoint=adj) for x in X])
+            try:
+                for tile in (16, 32, 64):
+                    dc.set_multi_tile_mode(tile)
+                    y = gop.apply_multi(X, prec=prec, adjoint=adj)
+                    assert _rel(y, ref) <= 2e-6, (prec, adj, tile)
+            finally:
+                dc.set_multi_tile_mode(0)
+    gop.close()
+
+
+def test_multi_pieces_range_and_nonfinite():
+    """Columns and sites of very different magnitude keep their own relative
+    accuracy; a non-finite entry reaches its column's neighbouring sites only."""
+    import numpy as np
+    gop, oop = make_pair((4, 2, 2, 2), 12, 3.0, mu=0.1, store=("f64", "f32"))
+    R = 20
+    X = torch.stack([rand_vec(oop.V, oop.n, 29, r) for r in range(R)]).cuda()
+    colscale = torch.logspace(-25, 25, R, dtype=torch.float64, device="cuda")
+    X = (X * colscale[:, None, None]).to(torch.complex64)
+    y = gop.apply_multi(X, prec="f32")
+    ref = gop.apply_multi(X.to(torch.complex128))
+    for r in range(R):
+        assert _rel(y[r].to(torch.complex128), ref[r]) <= 2e-6, r
+    nb = gop.neighbours()
+    for bad in (float("inf"), float("nan")):
+        Z = X.clone()
+        Z[7, 3, 5] = bad
+        z = gop.apply_multi(Z, prec="f32")
+        hit = np.zeros(oop.V, dtype=bool)
+        hit[3] = True
+        hit[nb[:, 3]] = True
+        fin = torch.isfinite(torch.view_as_real(z)).all(-1)
+        assert not bool(fin[7][torch.from_numpy(hit).cuda()].any())
+        assert bool(fin[7][torch.from_numpy(~hit).cuda()].all())
+        keep = [r for r in range(R) if r != 7]
+        assert torch.equal(z[keep], y[keep])
+    gop.close()
