@@ -13,6 +13,14 @@ __device__ inline T shfl_xor(T v, int m) {
   return __shfl_xor(v, m, kWave);
 }
 
+// Lane exchanges by DPP: lane ^ 1, lane ^ 2, the half-row mirror and a rotation
+// of a 16-lane row by 8.
+__device__ inline int dpp_xor1(int v) { return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, false); }
+__device__ inline int dpp_xor2(int v) { return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, false); }
+__device__ inline int dpp_hmirror(int v) { return __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, false); }
+__device__ inline int dpp_ror8(int v) { return __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, false); }
+
+
 // The two FP16 values of a packed 32-bit word, widened.
 __device__ inline float lo_h(uint32_t w) {
   return float(__builtin_bit_cast(_Float16, static_cast<unsigned short>(w & 0xffffu)));

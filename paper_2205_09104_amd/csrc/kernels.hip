@@ -96,93 +96,6 @@ __global__ __launch_bounds__(64) void k_finalize(const double* __restrict__ part
   finalize_value(partials, nparts, result, blockIdx.x);
 }
 
-// ------------------------------------------------------------------ layout
-// Tiled layout: block = 8 x 8 lane grid of T x T sub-tiles; lane l = lr*8+lc
-// owns rows lr*T .. lr*T+T-1 and columns lc*T .. lc*T+T-1; its element
-// e = a*T + b is (lr*T + a, lc*T + b).  Element e of lane l lives in 16-byte
-// unit (e / EPL)*64 + l, slot e % EPL.
-
-__device__ uint16_t f64_to_f16_rne(double x) {
-  const uint64_t b = __double_as_longlong(x);
-  const uint16_t sign = uint16_t((b >> 48) & 0x8000u);
-  const int exp = int((b >> 52) & 0x7ff);
-  const uint64_t mant = b & ((uint64_t(1) << 52) - 1);
-  if (exp == 0x7ff) return sign | 0x7c00u | (mant ? 0x200u : 0u);
-  if (exp == 0) return sign;  // FP64 subnormals are far below the FP16 range
-  const int e = exp - 1023;
-  if (e > 15) return sign | 0x7c00u;
-  const uint64_t m = mant | (uint64_t(1) << 52);
-  const int shift = (e >= -14) ? 42 : 42 + (-14 - e);
-  if (shift >= 64) return sign;
-  uint64_t keep = m >> shift;
-  const uint64_t rem = m & ((uint64_t(1) << shift) - 1);
-  const uint64_t half = uint64_t(1) << (shift - 1);
-  if (rem > half || (rem == half && (keep & 1))) keep += 1;
-  if (e >= -14) {
-    uint32_t hexp = uint32_t(e + 15);
-    if (keep >= (uint64_t(1) << 11)) {
-      keep >>= 1;
-      hexp += 1;
-    }
-    if (hexp >= 31) return sign | 0x7c00u;
-    return uint16_t(sign | (hexp << 10) | uint32_t(keep & 0x3ffu));
-  }
-  return uint16_t(sign | uint32_t(keep));  // subnormal (or the smallest normal)
-}
-
-__global__ void k_layout(const z64* __restrict__ self_in, const z64* __restrict__ hops_in,
-                         int V, int n, z64* __restrict__ o64, z32* __restrict__ o32,
-                         float* __restrict__ mx32, uint32_t* __restrict__ o16,
-                         float* __restrict__ sc16) {
-  const int blk = blockIdx.x;  // site*5 + slot
-  const int site = blk / 5, slot = blk % 5;
-  const size_t nn = size_t(n) * n;
-  const z64* src = (slot == 0) ? self_in + size_t(site) * nn
-                               : hops_in + (size_t(site) * 4 + (slot - 1)) * nn;
-  const int T = (n + 7) / 8;
-  const int TT = T * T;
-  // block max of |Re|, |Im| for the FP16 scale
-  __shared__ double smax[256];
-  double mx = 0.0;
-  for (size_t t = threadIdx.x; t < nn; t += blockDim.x) {
-    const z64 z = src[t];
-    mx = fmax(mx, fmax(fabs(z.re), fabs(z.im)));
-  }
-  smax[threadIdx.x] = mx;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) smax[threadIdx.x] = fmax(smax[threadIdx.x], smax[threadIdx.x + s]);
-    __syncthreads();
-  }
-  const float scale = float(smax[0]);
-  const double dscale = double(scale);
-  if (o16 && threadIdx.x == 0) sc16[blk] = scale;
-  if (o32 && threadIdx.x == 0) mx32[blk] = scale;
-  const int tt64 = ((TT + 0) / 1) * 1, tt32 = (TT + 1) / 2 * 2, tt16 = (TT + 3) / 4 * 4;
-  const int total = 64 * tt16;  // covers every padded position of every layout
-  for (int t = threadIdx.x; t < total; t += blockDim.x) {
-    const int lane = t & 63, e = t >> 6;
-    const int lr = lane >> 3, lc = lane & 7;
-    const int a = e / T, bcol = e - a * T;
-    const int i = lr * T + a, j = lc * T + bcol;
-    z64 z = mk(0.0, 0.0);
-    if (e < TT && i < n && j < n) z = src[size_t(i) * n + j];
-    if (o64 && e < tt64) o64[size_t(blk) * tt64 * 64 + size_t(e) * 64 + lane] = z;
-    if (o32 && e < tt32)
-      o32[size_t(blk) * tt32 * 64 + (size_t(e >> 1) * 64 + lane) * 2 + (e & 1)] =
-          mk(float(z.re), float(z.im));
-    if (o16) {
-      uint16_t cr = 0, ci = 0;
-      if (dscale > 0.0) {
-        cr = f64_to_f16_rne(z.re / dscale);
-        ci = f64_to_f16_rne(z.im / dscale);
-      }
-      o16[size_t(blk) * tt16 * 64 + (size_t(e >> 2) * 64 + lane) * 4 + (e & 3)] =
-          uint32_t(cr) | (uint32_t(ci) << 16);
-    }
-  }
-}
-
 __global__ void k_neighbours(int* nbr, int L0, int L1, int L2, int L3) {
   const int V = L0 * L1 * L2 * L3;
   const int x = blockIdx.x * blockDim.x + threadIdx.x;
@@ -274,11 +187,6 @@ struct VecOf<P64> {
 // column sums (over lr, lanes l^8, l^16, l^32) use a DPP row rotation by 8 and
 // the gfx950 permlane16/32 swaps, whose two outputs add to v[l] + v[l^16]
 // (resp. v[l^32]) in every lane.
-__device__ inline int dpp_xor1(int v) { return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, false); }
-__device__ inline int dpp_xor2(int v) { return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, false); }
-__device__ inline int dpp_hmirror(int v) { return __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, false); }
-__device__ inline int dpp_ror8(int v) { return __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, false); }
-
 template <int CTL>
 __device__ inline float dppf(float v) {
   int i = __float_as_int(v);
@@ -1158,134 +1066,6 @@ __device__ inline cx<VR> gather5(const cx<VR>* __restrict__ gbuf, size_t i, int 
 }
 
 // ------------------------------------------------------------------ block Jacobi
-// In-place Gauss-Jordan inversion (partial pivoting) of each site's self
-// block A_x + i*tm*Gamma5, one workgroup per site, matrix in LDS; the inverse
-// is written in the tiled layout of every requested precision.
-__device__ void write_tiled(const z64* M, int n, int blk, z64* o64, z32* o32, uint32_t* o16,
-                            float* sc16, double* red) {
-  const int T = (n + 7) / 8, TT = T * T;
-  const int tt32 = (TT + 1) / 2 * 2, tt16 = (TT + 3) / 4 * 4;
-  double mx = 0.0;
-  for (int t = threadIdx.x; t < n * n; t += blockDim.x)
-    mx = fmax(mx, fmax(fabs(M[t].re), fabs(M[t].im)));
-  red[threadIdx.x] = mx;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + s]);
-    __syncthreads();
-  }
-  const float scale = float(red[0]);
-  const double dscale = double(scale);
-  if (o16 && threadIdx.x == 0) sc16[blk] = scale;
-  for (int t = threadIdx.x; t < 64 * tt16; t += blockDim.x) {
-    const int lane = t & 63, e = t >> 6;
-    const int i = (lane >> 3) * T + e / T, j = (lane & 7) * T + e % T;
-    z64 z = mk(0.0, 0.0);
-    if (e < TT && i < n && j < n) z = M[i * n + j];
-    if (o64 && e < TT) o64[size_t(blk) * TT * 64 + size_t(e) * 64 + lane] = z;
-    if (o32 && e < tt32)
-      o32[size_t(blk) * tt32 * 64 + (size_t(e >> 1) * 64 + lane) * 2 + (e & 1)] =
-          mk(float(z.re), float(z.im));
-    if (o16) {
-      uint16_t cr = 0, ci = 0;
-      if (dscale > 0.0) {
-        cr = f64_to_f16_rne(z.re / dscale);
-        ci = f64_to_f16_rne(z.im / dscale);
-      }
-      o16[size_t(blk) * tt16 * 64 + (size_t(e >> 2) * 64 + lane) * 4 + (e & 3)] =
-          uint32_t(cr) | (uint32_t(ci) << 16);
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void k_invert_blocks(const z64* __restrict__ tiled64, int n,
-                                                       double tm, z64* o64, z32* o32,
-                                                       uint32_t* o16, float* sc16,
-                                                       int* __restrict__ singular) {
-  extern __shared__ z64 M[];               // n*n entries
-  __shared__ int perm[64];
-  __shared__ double red[256];
-  __shared__ int piv_row;
-  __shared__ z64 pivot_row[64];
-  __shared__ z64 pivot_col[64];
-  const int site = blockIdx.x;
-  const int nn = n * n;
-  const int T = (n + 7) / 8, TT = T * T;
-  const z64* src = tiled64 + size_t(site) * 5 * TT * 64;  // slot 0 of the site: A_x
-  for (int t = threadIdx.x; t < nn; t += blockDim.x) {
-    const int i = t / n, j = t % n;
-    const int lane = (i / T) * 8 + j / T, e = (i % T) * T + (j % T);
-    z64 z = src[size_t(e) * 64 + lane];
-    if (i == j) z.im += (i < (n >> 1)) ? tm : -tm;
-    M[t] = z;
-  }
-  __syncthreads();
-  for (int k = 0; k < n; ++k) {
-    // pivot: largest |M[i][k]| for i >= k (first wave; ties to the lower row)
-    if (threadIdx.x < 64) {
-      double best = -1.0;
-      int bi = k;
-      for (int i = k + int(threadIdx.x); i < n; i += 64) {
-        const double a = fabs(M[i * n + k].re) + fabs(M[i * n + k].im);
-        if (a > best) { best = a; bi = i; }
-      }
-      for (int o = 32; o > 0; o >>= 1) {
-        const double ob = __shfl_xor(best, o, 64);
-        const int oi = __shfl_xor(bi, o, 64);
-        if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
-      }
-      if (threadIdx.x == 0) {
-        piv_row = bi;
-        perm[k] = bi;
-        if (!(best > 0.0)) *singular = 1;
-      }
-    }
-    __syncthreads();
-    const int p = piv_row;
-    if (p != k)
-      for (int j = threadIdx.x; j < n; j += blockDim.x) {
-        const z64 a = M[k * n + j];
-        M[k * n + j] = M[p * n + j];
-        M[p * n + j] = a;
-      }
-    __syncthreads();
-    const z64 akk = M[k * n + k];
-    const double den = akk.re * akk.re + akk.im * akk.im;
-    const z64 d = den > 0.0 ? mk(akk.re / den, -akk.im / den) : mk(0.0, 0.0);  // 1 / a_kk
-    for (int j = threadIdx.x; j < n; j += blockDim.x) {
-      const z64 a = (j == k) ? mk(1.0, 0.0) : M[k * n + j];
-      pivot_row[j] = mk(a.re * d.re - a.im * d.im, a.re * d.im + a.im * d.re);
-      pivot_col[j] = M[j * n + k];
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < nn; t += blockDim.x) {
-      const int i = t / n, j = t % n;
-      if (i == k) {
-        M[t] = pivot_row[j];
-      } else {
-        const z64 f = pivot_col[i];
-        const z64 r = (j == k) ? mk(0.0, 0.0) : M[t];
-        const z64 pr = pivot_row[j];
-        // M[i][j] = (j == k ? 0 : M[i][j]) - f * pivot_row[j]
-        M[t] = mk(r.re - (f.re * pr.re - f.im * pr.im), r.im - (f.re * pr.im + f.im * pr.re));
-      }
-    }
-    __syncthreads();
-  }
-  // undo the row interchanges as column interchanges, last first
-  for (int k = n - 1; k >= 0; --k) {
-    const int p = perm[k];
-    if (p != k)
-      for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        const z64 a = M[i * n + k];
-        M[i * n + k] = M[i * n + p];
-        M[i * n + p] = a;
-      }
-    __syncthreads();
-  }
-  write_tiled(M, n, site, o64, o32, o16, sc16, red);
-}
-
 // out_x = M_x t_x with M_x the stored inverse and t either the sum of the 9
 // gbuf slots (t = D psi) or a plain vector; one wave per site; epilogue as in
 // the gather kernels (0 store, 1 poly_first, 2 poly).
@@ -2506,15 +2286,6 @@ inline unsigned grid_for(size_t N, int threads, unsigned cap = 4096) {
 
 // ====================================================================== launchers
 
-void launch_layout_blocks(const z64* self_in, const z64* hops_in, int V, int n, void* out64,
-                          void* out32, float* max32, void* out16, float* scales16,
-                          hipStream_t st) {
-  hipLaunchKernelGGL(k_layout, dim3(unsigned(V) * 5u), dim3(256), 0, st, self_in, hops_in, V, n,
-                     static_cast<z64*>(out64), static_cast<z32*>(out32), max32,
-                     static_cast<uint32_t*>(out16), scales16);
-  DC_HIP(hipGetLastError());
-}
-
 void launch_neighbours(int* nbr, int L0, int L1, int L2, int L3, hipStream_t st) {
   const int V = L0 * L1 * L2 * L3;
   hipLaunchKernelGGL(k_neighbours, dim3((V + 255) / 256), dim3(256), 0, st, nbr, L0, L1, L2, L3);
@@ -2556,18 +2327,6 @@ void launch_apply_blocks(Prec p, int n, int V, const void* blocks, const float* 
   if (p == P64) apply_T<P64>(n, V, blocks, scales, in, gbuf, nbr, tm, done, st, ev0, ev1);
   else if (p == P32) apply_T<P32>(n, V, blocks, scales, in, gbuf, nbr, tm, done, st, ev0, ev1);
   else apply_T<P16S>(n, V, blocks, scales, in, gbuf, nbr, tm, done, st, ev0, ev1);
-}
-
-void launch_invert_blocks(const void* tiled64, int V, int n, double tm, void* out64, void* out32,
-                          void* out16, float* scales16, int* singular, hipStream_t st) {
-  const size_t lds = size_t(n) * n * sizeof(z64);
-  DC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_invert_blocks),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
-  hipLaunchKernelGGL(k_invert_blocks, dim3(unsigned(V)), dim3(256), lds, st,
-                     static_cast<const z64*>(tiled64), n, tm,
-                     static_cast<z64*>(out64), static_cast<z32*>(out32),
-                     static_cast<uint32_t*>(out16), scales16, singular);
-  DC_HIP(hipGetLastError());
 }
 
 template <int P, bool FROMBUF, int EPI>

@@ -98,3 +98,52 @@ def test_multi_pieces_range_and_nonfinite():
         keep = [r for r in range(R) if r != 7]
         assert torch.equal(z[keep], y[keep])
     gop.close()
+
+
+# Self-block inverses in registers: every grid of entries per thread (n <= 16, 32, 48, 64) and
+# ragged sizes, on blocks that need their pivoting -- unitary ones with shuffled rows and
+# leading zeros, condition number 1, so B^{-1} v is exact to rounding (n eps and growth: 1e-12).
+@pytest.mark.parametrize("ntv", [1, 3, 8, 9, 16, 17, 24, 25, 31, 32])
+def test_block_inverse_pivoting(ntv):
+    import numpy as np
+    from paper_2205_09104_amd import CoarseOp
+    n, dims, V = 2 * ntv, (2, 2, 1, 2), 8
+    rng = np.random.default_rng(ntv)
+    A = np.zeros((V, n, n), dtype=np.complex128)
+    for x in range(V):
+        if x % 2:   # a permutation with phases: every pivot but one per column is zero
+            A[x, np.arange(n), rng.permutation(n)] = np.exp(2j * np.pi * rng.random(n))
+        else:       # two unitary blocks, rows shuffled
+            h = max(1, n // 3)
+            A[x, :h, :h] = np.linalg.qr(rng.normal(size=(h, h)) + 1j * rng.normal(size=(h, h)))[0]
+            A[x, h:, h:] = np.linalg.qr(rng.normal(size=(n - h, n - h)) +
+                                        1j * rng.normal(size=(n - h, n - h)))[0]
+            A[x] = A[x][rng.permutation(n)]
+    B = torch.zeros((V, 4, n, n), dtype=torch.complex128)
+    op = CoarseOp(torch.from_numpy(A).cuda(), B.cuda(), dims, store=("f64",))
+    v = rand_vec(V, n, 31, 0)
+    import ctypes as C
+    from paper_2205_09104_amd._lib import check, load
+    out = torch.empty_like(v, device="cuda")
+    vg = v.cuda()
+    check(load().dc_apply_block_jacobi(op._h, C.c_void_p(vg.data_ptr()),
+                                       C.c_void_p(out.data_ptr()), None))
+    torch.cuda.synchronize()
+    ref = np.linalg.solve(A, v.numpy()[:, :, None])[:, :, 0]
+    assert _rel(out.cpu(), torch.from_numpy(ref)) <= 1e-12
+    op.close()
+
+
+def test_block_inverse_singular_is_refused():
+    from paper_2205_09104_amd import CoarseOp, DcError
+    n, V = 6, 4
+    A = torch.eye(n, dtype=torch.complex128).repeat(V, 1, 1)
+    A[2, :, 4] = 0
+    op = CoarseOp(A.cuda(), torch.zeros((V, 4, n, n), dtype=torch.complex128).cuda(), (2, 2, 1, 1))
+    x = torch.ones((V, n), dtype=torch.complex128, device="cuda")
+    from paper_2205_09104_amd._lib import check, load
+    import ctypes as C
+    with pytest.raises(DcError):
+        check(load().dc_apply_block_jacobi(op._h, C.c_void_p(x.data_ptr()),
+                                           C.c_void_p(torch.empty_like(x).data_ptr()), None))
+    op.close()
