@@ -139,7 +139,6 @@ void launch_oddeven_split(Prec p, int n, int half_sites, const int* esite, const
 // yout[r] = D xin[r] for r < R (device arrays of R vector pointers, vectors in
 // the precision's vector type), MFMA based; g5io bit 0 multiplies inputs and
 // bit 1 outputs by Gamma5 (adjoint through Gamma5 D(-mu) Gamma5 with tm = -mu).
-size_t multi_lds_bytes(int n, bool dbl, int rb);
 // right-hand-side tile chosen for a multi-apply shape (0: not tuned yet), and
 // the tuning mode (0: autotune, 16/32/64: force that tile; 0 clears the table)
 int multi_tile_for(Prec p, int n, int rmax, unsigned sites);
