@@ -16,7 +16,7 @@ ROOT = os.path.dirname(HERE)
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libdcsolve.so")
 
-SOURCES = ["kernels.hip", "multi.hip", "setup.hip", "dense.cpp", "solver.cpp", "block.cpp", "capi.cpp"]
+SOURCES = ["kernels.hip", "multi.hip", "setup.hip", "krylov.hip", "dense.cpp", "solver.cpp", "block.cpp", "capi.cpp"]
 ARCH = os.environ.get("DCSOLVE_ARCH", "gfx950")
 
 # -packed-fp32-ops: keep hipcc from forming v_pk_*_f32 instructions
@@ -43,7 +43,7 @@ def _compile(src: str) -> str:
 
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(7, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         objs = list(ex.map(_compile, SOURCES))
     tmp = LIB + ".tmp"
     rocm_lib = os.path.join(os.path.dirname(os.path.dirname(_hipcc())), "lib")

@@ -13,6 +13,68 @@ __device__ inline T shfl_xor(T v, int m) {
   return __shfl_xor(v, m, kWave);
 }
 
+__device__ inline double gam(int i, int n) { return i < (n >> 1) ? 1.0 : -1.0; }
+
+template <typename R>
+__device__ inline cx<R> ld(const cx<R>* p) {
+  return *p;
+}
+
+// Block-wide sum of W doubles per thread (blockDim.x a multiple of 64, <= 1024),
+// written as this block's partial: partials[w * nblk + block].  A second
+// kernel (k_finalize) sums the partials of each value in a fixed order, so
+// every reduction is deterministic.
+template <int W>
+__device__ void block_partials_at(double (&v)[W], double* partials, int bid, int nblk) {
+  __shared__ double sh[16][W];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int nw = blockDim.x / kWave;
+#pragma unroll
+  for (int t = 0; t < W; ++t) {
+    double s = v[t];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += shfl_xor(s, o);
+    if (lane == 0) sh[wave][t] = s;
+  }
+  __syncthreads();
+  if (threadIdx.x < W) {
+    double s = 0.0;
+    for (int w = 0; w < nw; ++w) s += sh[w][threadIdx.x];
+    partials[size_t(threadIdx.x) * nblk + bid] = s;
+  }
+}
+
+template <int W>
+__device__ void block_partials(double (&v)[W], double* partials) {
+  block_partials_at<W>(v, partials, blockIdx.x + blockIdx.y * gridDim.x, gridDim.x * gridDim.y);
+}
+
+// result[v] = sum_b partials[v * nparts + b]; one 64-lane wave per value.
+__device__ inline void finalize_value(const double* __restrict__ partials, int nparts,
+                                      double* __restrict__ result, int v) {
+  double s = 0.0;
+  for (int b = threadIdx.x; b < nparts; b += 64) s += partials[size_t(v) * nparts + b];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += shfl_xor(s, o);
+  if (threadIdx.x == 0) result[v] = s;
+}
+
+inline unsigned grid_for(size_t N, int threads, unsigned cap = 4096) {
+  size_t b = (N + threads - 1) / threads;
+  if (b < 1) b = 1;
+  if (b > cap) b = cap;
+  return unsigned(b);
+}
+
+// blocks of a single-value reduction over N elements: >= 4 elements per
+// thread, at most 512 partials
+inline unsigned red_blocks(size_t N) {
+  size_t b = (N + 1023) / 1024;
+  if (b < 1) b = 1;
+  if (b > 512) b = 512;
+  return unsigned(b);
+}
+
 // Lane exchanges by DPP: lane ^ 1, lane ^ 2, the half-row mirror and a rotation
 // of a 16-lane row by 8.
 __device__ inline int dpp_xor1(int v) { return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, false); }

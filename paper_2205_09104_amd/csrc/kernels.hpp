@@ -24,6 +24,9 @@ struct Reducer {
   double* partials = nullptr;   // capacity: kRedCap doubles
 };
 constexpr int kRedCap = 65536;
+// result[v] = sum over the nparts partials of value v, v < nvals
+void launch_finalize(const double* partials, int nvals, int nparts, double* result,
+                     const int* done, hipStream_t st);
 
 // ---------------------------------------------------------------- operator
 // Re-lay out FP64 input blocks (self [V][n][n] + hops [V][4][n][n], device,
@@ -180,11 +183,6 @@ void launch_multidot(Prec p, const void* b0, int q0, const void* b1, int q1, siz
 void launch_multiaxpy(Prec p, void* w, const void* b0, int q0, const void* b1, int q1,
                       size_t N, const double* coef, int want_norm, Reducer red,
                       double* result, const int* done, hipStream_t st);
-// w = (w - sum_q coef_q basis_q) * (*scale) for Arnoldi step j: runs only if
-// that step's bookkeeping ran (*jdone == j + 1); no norm.
-void launch_multiaxpy_scaled(Prec p, void* w, const void* b0, int q0, const void* b1, int q1,
-                             size_t N, const double* coef, const double* scale, const int* jdone,
-                             int j, hipStream_t st);
 // out_r (= or +=) sum_q coef[r*Q + q] basis_q for r < R, Q = q0 + q1; coef
 // device complex; outputs are R vectors with stride N, not overlapping the
 // basis.  Products and sums in FP64 (16 or more outputs: on MFMA tiles).
@@ -262,19 +260,27 @@ struct ArnoldiDev {
   int* done;        // cycle flag
   int* jdone;       // steps completed
   int* brk_flag;    // 1 if the cycle ended by breakdown
+  int* go = nullptr;     // j + 1 once step j's first kernel ran (launch_gram_schmidt)
   int* hdone = nullptr;  // optional host-mapped copy of the done flag (set to 1 with it)
   double* hest = nullptr;  // optional host-mapped per-step estimates: hest[j] after step j
   const double* target_dev = nullptr;  // optional: the stopping target read from device memory
                                        // (replaces the value argument; graph replays)
 };
-// c2 null: the single-sync process (one pass of coefficients c1, whose entry
-// kC + j + 1 is ||A v_j||^2; h_{j+1,j}^2 = ||A v_j||^2 - sum |c1|^2; nrm2 unused).
 void launch_arnoldi_finish(ArnoldiDev a, int steps, int kC, int j, const double* c1,
                            const double* c2, const double* nrm2, double target, double brk,
                            hipStream_t st);
 // beta_dev: take beta from device memory instead
 void launch_arnoldi_init(ArnoldiDev a, double beta, hipStream_t st,
                          const double* beta_dev = nullptr);
+
+// One orthogonalisation step of a single column: w = V_{j+1} against [b0 b1] by
+// classical Gram-Schmidt twice (single_sync: the single-sync process), the
+// bookkeeping of step j and the normalisation.  The
+// coefficients of the passes land in res1 and res2 (2 (q0 + q1 + 1) doubles each).
+void launch_gram_schmidt(Prec p, const void* b0, int q0, const void* b1, int q1, size_t N, void* w,
+                         Reducer red, double* res1, double* res2, const ArnoldiDev& a,
+                         bool single_sync, int steps, int kC, int j, double target, double brk,
+                         hipStream_t st);
 
 // Batched Gram-Schmidt: the launches of one classical Gram-Schmidt step (as
 // launch_multidot / launch_multiaxpy / launch_arnoldi_finish /

@@ -916,6 +916,7 @@ struct Krylov {
     ad.done = ip;
     ad.jdone = ip + 1;
     ad.brk_flag = ip + 2;
+    ad.go = ip + 3;
   }
 
   Z* V(int j) const { return Vb + size_t(j) * N; }
@@ -1050,20 +1051,18 @@ struct Krylov {
     return std::sqrt(std::max(h, 0.0));
   }
 
-  // Gram-Schmidt of V(j+1) against [C, V(0..j)] (classical, applied twice),
-  // then the bookkeeping kernel and normalisation.
+  // Gram-Schmidt of V(j+1) against [C, V(0..j)] (classical, applied twice, or
+  // the single-sync process of Sec. 3.5), the bookkeeping and the normalisation.
   void orth_step(int j, int kC, int steps, double target) {
+    launch_gram_schmidt(p, kC ? Cv() : nullptr, kC, V(0), j + 1, N, V(j + 1), op.red(), res1, res2,
+                        ad, ortho_now == 1, steps, kC, j, target, brk, st);
+  }
+
+  // The same with a launch per pass, as lockstep batches make it for each column
+  // (their batched launches have these sums, column for column).
+  void orth_step_column(int j, int kC, int steps, double target) {
     Z* w = V(j + 1);
     const Z* Cb = kC ? Cv() : nullptr;
-    if (ortho_now == 1) {
-      // single-sync process (Sec. 3.5): one reduction yields the coefficients
-      // and ||A v_j||^2, h_{j+1,j} follows from their difference, and the
-      // update and normalisation are one pass
-      launch_multidot(p, Cb, kC, V(0), j + 1, N, w, 1, op.red(), res1, ad.done, st);
-      launch_arnoldi_finish(ad, steps, kC, j, res1, nullptr, nullptr, target, brk, st);
-      launch_multiaxpy_scaled(p, w, Cb, kC, V(0), j + 1, N, res1, ad.inv_h, ad.jdone, j, st);
-      return;
-    }
     launch_multidot(p, Cb, kC, V(0), j + 1, N, w, 1, op.red(), res1, ad.done, st);
     launch_multiaxpy(p, w, Cb, kC, V(0), j + 1, N, res1, 0, op.red(), nrm, ad.done, st);
     launch_multidot(p, Cb, kC, V(0), j + 1, N, w, 0, op.red(), res2, ad.done, st);
@@ -2267,14 +2266,14 @@ struct Batch {
       for (size_t gi = 0; gi < g.size(); ++gi) {
         Group& gr = g[gi];
         for (size_t a = 0; a < gr.act.size(); ++a)
-          gr.K[gr.act[a]]->orth_step(j, gr.var->kcur, steps, target[gi][a]);
+          gr.K[gr.act[a]]->orth_step_column(j, gr.var->kcur, steps, target[gi][a]);
       }
     }
   }
 
   // Step j's Gram-Schmidt (classical, twice) of every active column, one
   // launch per pass for up to kOrthCols columns of equal deflation-space size:
-  // the launches of Krylov::orth_step with ortho = 0, for many columns at once
+  // the launches of Krylov::orth_step_column, for many columns at once
   // (same sums, so the same results), each column with its own slice of the
   // batch's reduction partials.
   void orth_batched(int j, int steps, const std::vector<std::vector<double>>& target) {

@@ -147,3 +147,46 @@ def test_block_inverse_singular_is_refused():
         check(load().dc_apply_block_jacobi(op._h, C.c_void_p(x.data_ptr()),
                                            C.c_void_p(torch.empty_like(x).data_ptr()), None))
     op.close()
+
+
+# Gram-Schmidt steps: bases through 1, 2, 4, 8, 16, 32, 48, 64 and beyond 64 vectors, and
+# vectors of less than two tiles (odd length), of one tile per workgroup, and of several
+# (partials summed by the next kernel or by a launch of their own).  The bound is the one
+# of the other Hessenberg comparison; the oracle's own H moves by less than 1e-12 of its
+# largest entry under a start vector perturbed by 1e-13.  Single-sync: that process's
+# bound, over the steps where one pass keeps the basis orthogonal.
+@pytest.mark.parametrize("dims,ntv,steps,ortho,tol", [
+    ((3, 2, 2, 2), 2, 30, 0, 1e-10), ((4, 4, 4, 4), 9, 70, 0, 1e-10),
+    ((8, 6, 6, 6), 10, 40, 0, 1e-10), ((3, 2, 2, 2), 2, 12, 1, 1e-9),
+    ((4, 4, 4, 4), 9, 12, 1, 1e-9), ((8, 6, 6, 6), 10, 18, 1, 1e-9)])
+def test_gram_schmidt_steps(dims, ntv, steps, ortho, tol):
+    from oracle import operator as dop
+    from oracle.krylov import arnoldi
+    from paper_2205_09104_amd import Opts
+    gop, oop = make_pair(dims, ntv, 3.0, mu=0.1)
+    v = rand_vec(oop.V, oop.n, 80)
+    ref = arnoldi(lambda u: dop.apply(oop, u.reshape(oop.V, oop.n)).reshape(-1),
+                  v.numpy().reshape(-1), steps, "mgs").Hbar
+    for _ in range(2):
+        H, s = gop.arnoldi(v.cuda(), steps, Opts(m=steps, ortho=ortho))
+        assert s == steps
+        err = float(abs(H - ref).max() / abs(ref).max())
+        log(f"  gram-schmidt {dims} n {oop.n} steps {steps} ortho {ortho}: {err:.1e}")
+        assert err <= tol
+    gop.close()
+
+
+# The same steps on FP32 vectors, with a recycle space before the basis: mixed solves
+# whose cycles pass 64 vectors, to the tolerance on the FP64 true residual.
+@pytest.mark.parametrize("ortho", [0, 1])
+def test_gram_schmidt_fp32_recycled(ortho):
+    from paper_2205_09104_amd import Opts
+    from .helpers import oracle_relres
+    gop, oop = make_pair((4, 4, 4, 4), 5, 3.0, mu=0.1, store=("f64", "f32", "f16s"))
+    o = Opts(m=80, k=8, d=4, prec="f32", outer=1, inner_tol=1e-5, seed=1, ortho=ortho)
+    for r in range(2):
+        b = rand_vec(oop.V, oop.n, 81, r)
+        x, st, rc = gop.solve(b.cuda(), 1e-10, o)
+        assert rc == 0 and st[0]["rel_res_true"] <= 1e-10, st
+        assert oracle_relres(oop, x.cpu().numpy(), b.numpy()) <= 1e-10
+    gop.close()
