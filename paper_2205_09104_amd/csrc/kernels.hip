@@ -305,40 +305,38 @@ __device__ inline void tile_products(const TileRegs<T, P>& R, const cx<A> (&pc)[
 // One stored block of one site, processed by one wave.  Full lattice (the
 // default): the self block writes slot 4 of gbuf[x]; a hop block B[x,mu]
 // writes B psi_{x+mu} into slot 5+mu of gbuf[x] and Gamma5 B^H Gamma5 psi_x
-// into slot mu of gbuf[x+mu].  The odd-even reduction selects one direction
-// (DIRS: 1 forward only, 2 backward only), addresses vectors and gbuf by the
-// compressed index x / 2 of one parity (COMP) and may negate the products (NEG).
-template <int T, int P, bool FULL, bool HOP, int DIRS = 3, bool COMP = false, bool NEG = false>
+// into slot mu of gbuf[x+mu].  g5: Gamma5 before and after (the adjoint through
+// Gamma5 D(-mu) Gamma5), as signs of the products' inputs and outputs.
+template <int T, int P, bool FULL, bool HOP>
 __device__ __forceinline__ void apply_one_block(
     const uint4* __restrict__ bp, const float* __restrict__ scales,
     const cx<typename VecOf<P>::R>* __restrict__ psi, cx<typename VecOf<P>::R>* __restrict__ gbuf,
-    int item, int site, int slot, int src, int n, double tm) {
+    int item, int site, int slot, int src, int n, double tm, int g5, int stream) {
   using A = typename Tile<T, P>::A;
   using VR = typename VecOf<P>::R;
-  constexpr bool DOF = !HOP || (DIRS & 1);
-  constexpr bool DOG = HOP && (DIRS & 2);
+  constexpr bool DOG = HOP;
   const int lane = threadIdx.x;
   const int lr = lane >> 3, lc = lane & 7;
-  const int vsite = COMP ? (site >> 1) : site, vsrc = COMP ? (src >> 1) : src;
   TileRegs<T, P> R;
-  R.load(bp, lane);
+  if (stream) R.load_stream(bp, lane);
+  else R.load(bp, lane);
   cx<A> pc[T], pr[T];
   A npc_im[T], npr_re[T];
 #pragma unroll
   for (int q = 0; q < T; ++q) {
     const int col = lc * T + q;
     pc[q] = mk(A(0), A(0));
-    if (DOF && (FULL || col < n)) {
-      const cx<VR> z = psi[size_t(HOP ? vsrc : vsite) * n + col];
-      pc[q] = mk(A(z.re), A(z.im));
+    if (FULL || col < n) {
+      const cx<VR> z = psi[size_t(HOP ? src : site) * n + col];
+      pc[q] = (g5 && col >= (n >> 1)) ? mk(A(-z.re), A(-z.im)) : mk(A(z.re), A(z.im));
     }
     npc_im[q] = -pc[q].im;
     pr[q] = mk(A(0), A(0));
     if (DOG) {
       const int row = lr * T + q;
       if (FULL || row < n) {
-        const cx<VR> z = psi[size_t(vsite) * n + row];
-        pr[q] = (row < (n >> 1)) ? mk(A(z.re), A(z.im)) : mk(A(-z.re), A(-z.im));
+        const cx<VR> z = psi[size_t(site) * n + row];
+        pr[q] = (g5 || row < (n >> 1)) ? mk(A(z.re), A(z.im)) : mk(A(-z.re), A(-z.im));
       }
     }
     npr_re[q] = -pr[q].re;
@@ -349,31 +347,30 @@ __device__ __forceinline__ void apply_one_block(
     f[q] = mk(A(0), A(0));
     g[q] = mk(A(0), A(0));
   }
-  tile_products<T, P, DOF, DOG>(R, pc, npc_im, pr, npr_re, f, g);
+  tile_products<T, P, true, DOG>(R, pc, npc_im, pr, npr_re, f, g);
   A s = A(1);
   if (P == P16S) s = A(scales[item]);
-  if (NEG) s = -s;
-  if constexpr (DOF) {
+#pragma unroll
+  for (int q = 0; q < T; ++q) {
+    f[q].re = sum_row8(f[q].re) * s;
+    f[q].im = sum_row8(f[q].im) * s;
+  }
+  if (lc == 0) {
+    cx<VR>* dst = gbuf + (size_t(site) * kSlots + (HOP ? 4 + slot : 4)) * n;
 #pragma unroll
     for (int q = 0; q < T; ++q) {
-      f[q].re = sum_row8(f[q].re) * s;
-      f[q].im = sum_row8(f[q].im) * s;
-    }
-    if (lc == 0) {
-      cx<VR>* dst = gbuf + (size_t(vsite) * kSlots + (HOP ? 4 + slot : 4)) * n;
-#pragma unroll
-      for (int q = 0; q < T; ++q) {
-        const int row = lr * T + q;
-        if (FULL || row < n) {
-          cx<A> v = f[q];
-          if (!HOP && tm != 0.0) {  // i * tm * Gamma5 psi_x in the accumulation precision
-            const A t = A(row < (n >> 1) ? tm : -tm);
-            const cx<VR> z = psi[size_t(vsite) * n + row];
-            v.re -= t * A(z.im);
-            v.im += t * A(z.re);
-          }
-          dst[row] = mk(VR(v.re), VR(v.im));
+      const int row = lr * T + q;
+      if (FULL || row < n) {
+        const bool low = row >= (n >> 1);
+        cx<A> v = f[q];
+        if (g5 && low) v = mk(-v.re, -v.im);
+        if (!HOP && tm != 0.0) {  // i * tm * Gamma5 psi_x in the accumulation precision
+          const A t = A(low ? -tm : tm);
+          const cx<VR> z = psi[size_t(site) * n + row];
+          v.re -= t * A(z.im);
+          v.im += t * A(z.re);
         }
+        dst[row] = mk(VR(v.re), VR(v.im));
       }
     }
   }
@@ -384,12 +381,12 @@ __device__ __forceinline__ void apply_one_block(
       g[q].im = sum_col8(g[q].im) * s;
     }
     if (lr == 0) {
-      cx<VR>* dst = gbuf + (size_t(vsrc) * kSlots + (slot - 1)) * n;  // x + mu receives it
+      cx<VR>* dst = gbuf + (size_t(src) * kSlots + (slot - 1)) * n;  // x + mu receives it
 #pragma unroll
       for (int q = 0; q < T; ++q) {
         const int col = lc * T + q;
         if (FULL || col < n) {
-          const A gg = (col < (n >> 1)) ? A(1) : A(-1);
+          const A gg = (g5 || col < (n >> 1)) ? A(1) : A(-1);
           dst[col] = mk(VR(gg * g[q].re), VR(gg * g[q].im));
         }
       }
@@ -401,12 +398,15 @@ __device__ __forceinline__ void apply_one_block(
 // once with 16-byte loads (1 KB contiguous per load instruction) and forms
 // from registers both the forward product B psi_{x+mu} (row sums) and the
 // backward product Gamma5 B^H Gamma5 psi_x (column sums).  No barrier: waves
-// of different sites overlap their loads with each other's arithmetic.
+// of different sites overlap their loads with each other's arithmetic.  HBM bound
+// with blocks beyond the last-level cache: 16^4, n = 48, FP16: 572 us, 5.5 TB/s of
+// block and vector bytes (607 with cached loads); 8^4, n = 48, FP64: 133 us (149).
 template <int T, int P, bool FULL>
 __global__ __launch_bounds__(64) void k_apply_blocks(
     const void* __restrict__ blocks, const float* __restrict__ scales,
     const cx<typename VecOf<P>::R>* __restrict__ psi, cx<typename VecOf<P>::R>* __restrict__ gbuf,
-    const int* __restrict__ nbr, int V, int n, int chunk, double tm, const int* __restrict__ done) {
+    const int* __restrict__ nbr, int V, int n, int chunk, double tm, int g5,
+    int stream, const int* __restrict__ done) {
   if (done && *done) return;
   // XCD-aware order: workgroup b runs on XCD b % 8; each XCD gets a
   // contiguous range of (site, block) items, so a site's blocks are streamed
@@ -418,10 +418,10 @@ __global__ __launch_bounds__(64) void k_apply_blocks(
   const size_t blk_units = size_t(Tile<T, P>::UNITS) * 64;
   const uint4* bp = static_cast<const uint4*>(blocks) + size_t(item) * blk_units;
   if (slot == 0) {
-    apply_one_block<T, P, FULL, false>(bp, scales, psi, gbuf, item, site, 0, site, n, tm);
+    apply_one_block<T, P, FULL, false>(bp, scales, psi, gbuf, item, site, 0, site, n, tm, g5, stream);
   } else {
     const int src = nbr[(slot - 1) * V + site];
-    apply_one_block<T, P, FULL, true>(bp, scales, psi, gbuf, item, site, slot, src, n, tm);
+    apply_one_block<T, P, FULL, true>(bp, scales, psi, gbuf, item, site, slot, src, n, tm, g5, stream);
   }
 }
 
@@ -436,11 +436,12 @@ __global__ __launch_bounds__(64) void k_apply_blocks(
 // One wave's product of a stored block (registers R, scale s) with the
 // n-vector v, into dst (LDS): DIR 1 forward B v (row sums), DIR 2 backward
 // Gamma5 B^H Gamma5 v (column sums), DIR 0 self block B v + i tm Gamma5 v.
+// g5 bit 0 multiplies v by Gamma5 first, bit 1 the product.
 template <int T, int P, bool FULL, int DIR>
 __device__ __forceinline__ void wave_product(const TileRegs<T, P>& R, typename Tile<T, P>::A s,
                                              const cx<typename VecOf<P>::R>* __restrict__ v,
                                              cx<typename VecOf<P>::R>* dst, int n, double tm,
-                                             int lane) {
+                                             int lane, int g5 = 0) {
   using A = typename Tile<T, P>::A;
   using VR = typename VecOf<P>::R;
   constexpr bool DOF = DIR != 2, DOG = DIR == 2;
@@ -455,14 +456,14 @@ __device__ __forceinline__ void wave_product(const TileRegs<T, P>& R, typename T
       const int col = lc * T + q;
       if (FULL || col < n) {
         const cx<VR> z = v[col];
-        pc[q] = mk(A(z.re), A(z.im));
+        pc[q] = ((g5 & 1) && col >= (n >> 1)) ? mk(A(-z.re), A(-z.im)) : mk(A(z.re), A(z.im));
       }
     }
     if (DOG) {
       const int row = lr * T + q;
       if (FULL || row < n) {
         const cx<VR> z = v[row];
-        pr[q] = (row < (n >> 1)) ? mk(A(z.re), A(z.im)) : mk(A(-z.re), A(-z.im));
+        pr[q] = ((g5 & 1) || row < (n >> 1)) ? mk(A(z.re), A(z.im)) : mk(A(-z.re), A(-z.im));
       }
     }
     npc_im[q] = -pc[q].im;
@@ -482,9 +483,12 @@ __device__ __forceinline__ void wave_product(const TileRegs<T, P>& R, typename T
       for (int q = 0; q < T; ++q) {
         const int row = lr * T + q;
         if (FULL || row < n) {
+          const bool low = row >= (n >> 1);
           cx<A> w = f[q];
+          if ((g5 & 2) && low) w = mk(-w.re, -w.im);
           if (DIR == 0 && tm != 0.0) {  // i * tm * Gamma5 v in the accumulation precision
-            const A t = A(row < (n >> 1) ? tm : -tm);
+            const bool neg = low && (g5 & 1) == (g5 >> 1);
+            const A t = A(neg ? -tm : tm);
             const cx<VR> z = v[row];
             w.re -= t * A(z.im);
             w.im += t * A(z.re);
@@ -504,7 +508,7 @@ __device__ __forceinline__ void wave_product(const TileRegs<T, P>& R, typename T
       for (int q = 0; q < T; ++q) {
         const int col = lc * T + q;
         if (FULL || col < n) {
-          const A gg = (col < (n >> 1)) ? A(1) : A(-1);
+          const A gg = ((g5 & 2) || col < (n >> 1)) ? A(1) : A(-1);
           dst[col] = mk(VR(gg * g[q].re), VR(gg * g[q].im));
         }
       }
@@ -519,6 +523,54 @@ __device__ __forceinline__ const uint4* block_ptr(const void* blocks, size_t ite
   return static_cast<const uint4*>(blocks) + item * (size_t(Tile<T, P>::UNITS) * 64);
 }
 
+// The full-lattice apply in one launch, for operators whose blocks stay in the caches:
+// workgroup per site, wave 0 the self block, waves 1-4 the forward hops, 5-8 the
+// backward hops, summed in the order of the two-kernel form (equal bit for bit).
+// Every hop block is read twice, but there is no second launch and nothing goes
+// through memory between the two: 4^4, n = 16, FP64: 6.2 us in two kernels -> 3.4.
+template <int T, int P, bool FULL>
+__global__ __launch_bounds__(64 * kRedWaves) void k_apply_site(
+    const void* __restrict__ blocks, const float* __restrict__ scales,
+    const cx<typename VecOf<P>::R>* __restrict__ psi, cx<typename VecOf<P>::R>* __restrict__ out,
+    const int* __restrict__ nbr, int V, int n, int chunk, double tm, int g5,
+    const int* __restrict__ done) {
+  using A = typename Tile<T, P>::A;
+  using VR = typename VecOf<P>::R;
+  __shared__ cx<VR> part[kRedWaves][64];
+  if (done && *done) return;
+  const int b = blockIdx.x;
+  const int x = (b & 7) * chunk + (b >> 3);   // contiguous sites per XCD
+  if (x >= V) return;
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  TileRegs<T, P> R;
+  if (w < 5) {
+    const int item = 5 * x + w;
+    R.load(block_ptr<T, P>(blocks, size_t(item)), lane);
+    const A s = (P == P16S) ? A(scales[item]) : A(1);
+    if (w == 0) {
+      wave_product<T, P, FULL, 0>(R, s, psi + size_t(x) * n, part[0], n, tm, lane, g5);
+    } else {
+      const int src = nbr[(w - 1) * V + x];
+      wave_product<T, P, FULL, 1>(R, s, psi + size_t(src) * n, part[w], n, 0.0, lane, g5);
+    }
+  } else {
+    const int src = nbr[(w - 1) * V + x];
+    const int item = 5 * src + w - 4;
+    R.load(block_ptr<T, P>(blocks, size_t(item)), lane);
+    const A s = (P == P16S) ? A(scales[item]) : A(1);
+    wave_product<T, P, FULL, 2>(R, s, psi + size_t(src) * n, part[w], n, 0.0, lane, g5);
+  }
+  __syncthreads();
+  if (w != 0 || lane >= n) return;
+  cx<VR> t = part[0][lane];
+#pragma unroll
+  for (int k = 1; k < kRedWaves; ++k) {
+    t.re += part[k][lane].re;
+    t.im += part[k][lane].im;
+  }
+  out[size_t(x) * n + lane] = t;
+}
+
 // t_o = A_o^{-1} D_oe x_e.  Workgroup per odd row r (site x = osite[r]):
 // waves 0-3 the forward hops B[x,mu] x_e(x+mu), waves 4-7 the backward hops
 // Gamma5 B[x-mu,mu]^H Gamma5 x_e(x-mu), then wave 8 applies the inverse of
@@ -530,7 +582,7 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduced_oe(
     const void* __restrict__ inv, const float* __restrict__ invsc,
     const cx<typename VecOf<P>::R>* __restrict__ x_e, cx<typename VecOf<P>::R>* __restrict__ t_o,
     const int* __restrict__ nbr, const int* __restrict__ osite, int V, int n, int chunk,
-    const int* __restrict__ done) {
+    int g5, const int* __restrict__ done) {
   using A = typename Tile<T, P>::A;
   using VR = typename VecOf<P>::R;
   __shared__ cx<VR> part[8][64];
@@ -546,14 +598,14 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduced_oe(
     R.load(block_ptr<T, P>(blocks, size_t(item)), lane);
     const A s = (P == P16S) ? A(scales[item]) : A(1);
     const int src = nbr[w * V + x];
-    wave_product<T, P, FULL, 1>(R, s, x_e + size_t(src >> 1) * n, part[w], n, 0.0, lane);
+    wave_product<T, P, FULL, 1>(R, s, x_e + size_t(src >> 1) * n, part[w], n, 0.0, lane, g5 & 1);
   } else if (w < 8) {
     const int mu = w - 4;
     const int y = nbr[(4 + mu) * V + x];
     const int item = 5 * y + 1 + mu;
     R.load(block_ptr<T, P>(blocks, size_t(item)), lane);
     const A s = (P == P16S) ? A(scales[item]) : A(1);
-    wave_product<T, P, FULL, 2>(R, s, x_e + size_t(y >> 1) * n, part[w], n, 0.0, lane);
+    wave_product<T, P, FULL, 2>(R, s, x_e + size_t(y >> 1) * n, part[w], n, 0.0, lane, g5 & 1);
   }
   __syncthreads();
   if (w != 8) return;
@@ -651,7 +703,7 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduced_eo(
     const cx<typename VecOf<P>::R>* x_e, const cx<typename VecOf<P>::R>* __restrict__ t_o,
     const int* __restrict__ nbr, const int* __restrict__ esite, int V, int n, int chunk, double tm,
     cx<typename VecOf<P>::R>* out, const cx<typename VecOf<P>::R>* e, cx<typename VecOf<P>::R>* y,
-    z64 c0, z64 ca, z64 cb, const int* __restrict__ done) {
+    z64 c0, z64 ca, z64 cb, int g5, const int* __restrict__ done) {
   using A = typename Tile<T, P>::A;
   using VR = typename VecOf<P>::R;
   __shared__ cx<VR> part[kRedWaves][64];
@@ -680,7 +732,7 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduced_eo(
       const int item = 5 * x;
       R.load(block_ptr<T, P>(blocks, size_t(item)), lane);
       const A s = (P == P16S) ? A(scales[item]) : A(1);
-      wave_product<T, P, FULL, 0>(R, s, x_e + size_t(r) * n, part[0], n, tm, lane);
+      wave_product<T, P, FULL, 0>(R, s, x_e + size_t(r) * n, part[0], n, tm, lane, g5 & 1);
     } else {
       for (int i = lane; i < n; i += 64) part[0][i] = mk(VR(0), VR(0));
     }
@@ -742,9 +794,11 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduced_eo(
     cx<VR> t = mk(VR(mine.re), VR(mine.im));
     if (x_e) {
       const cx<VR> xv = x_e[i];
-      t.re += xv.re;
-      t.im += xv.im;
+      const VR sx = VR((g5 && row >= (n >> 1)) ? -1 : 1);
+      t.re += sx * xv.re;
+      t.im += sx * xv.im;
     }
+    if (g5 && row >= (n >> 1)) t = mk(-t.re, -t.im);
     reduced_epilogue<EPI>(i, t, out, e, y, c0, ca, cb);
   } else {
     for (int c = lane; c < n; c += 64) {
@@ -754,6 +808,7 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduced_eo(
         t.re += part[k][c].re;
         t.im += part[k][c].im;
       }
+      if (g5 && c >= (n >> 1)) t = mk(-t.re, -t.im);
       reduced_epilogue<EPI>(size_t(r) * n + c, t, out, e, y, c0, ca, cb);
     }
   }
@@ -796,7 +851,7 @@ __global__ __launch_bounds__(512, (scatter_min_waves<T, P>())) void k_reduced_sc
     const void* __restrict__ inv, const float* __restrict__ invsc,
     const cx<typename VecOf<P>::R>* __restrict__ x_e, cx<typename VecOf<P>::R>* __restrict__ hp,
     const int* __restrict__ nbr, const int* __restrict__ osite, int V, int n, int chunk,
-    const int* __restrict__ done) {
+    int g5, const int* __restrict__ done) {
   using A = typename Tile<T, P>::A;
   using VR = typename VecOf<P>::R;
   constexpr int UNITS = Tile<T, P>::UNITS;
@@ -826,7 +881,7 @@ __global__ __launch_bounds__(512, (scatter_min_waves<T, P>())) void k_reduced_sc
     R.load_stream(block_ptr<T, P>(blocks, size_t(item)), lane);
     if (P == P16S) s = A(scales[item]);
     const int src = nbr[w * V + x];
-    wave_product<T, P, FULL, 1>(R, s, x_e + size_t(src >> 1) * n, part[w], n, 0.0, lane);
+    wave_product<T, P, FULL, 1>(R, s, x_e + size_t(src >> 1) * n, part[w], n, 0.0, lane, g5 & 1);
     dst = (size_t(src >> 1) * 8 + 4 + w) * n;        // backward hop mu = w of even x + mu
   } else {
     const int mu = w - 4;
@@ -834,7 +889,7 @@ __global__ __launch_bounds__(512, (scatter_min_waves<T, P>())) void k_reduced_sc
     const int item = 5 * y + 1 + mu;
     R.load_stream(block_ptr<T, P>(blocks, size_t(item)), lane);
     if (P == P16S) s = A(scales[item]);
-    wave_product<T, P, FULL, 2>(R, s, x_e + size_t(y >> 1) * n, part[w], n, 0.0, lane);
+    wave_product<T, P, FULL, 2>(R, s, x_e + size_t(y >> 1) * n, part[w], n, 0.0, lane, g5 & 1);
     dst = (size_t(y >> 1) * 8 + mu) * n;             // forward hop mu of even x - mu
   }
   __syncthreads();
@@ -909,7 +964,7 @@ __global__ __launch_bounds__(64) void k_reduced_gather(
     const cx<typename VecOf<P>::R>* x_e, const cx<typename VecOf<P>::R>* __restrict__ hp,
     const int* __restrict__ esite, int V, int n, int chunk, double tm,
     cx<typename VecOf<P>::R>* out, const cx<typename VecOf<P>::R>* e, cx<typename VecOf<P>::R>* y,
-    z64 c0, z64 ca, z64 cb, const int* __restrict__ done) {
+    z64 c0, z64 ca, z64 cb, int g5, const int* __restrict__ done) {
   using A = typename Tile<T, P>::A;
   using VR = typename VecOf<P>::R;
   __shared__ cx<VR> self_part[64];
@@ -964,16 +1019,18 @@ __global__ __launch_bounds__(64) void k_reduced_gather(
     cx<VR> o = mk(VR(mine.re), VR(mine.im));
     if (x_e) {
       const cx<VR> xv = x_e[i];
-      o.re += xv.re;
-      o.im += xv.im;
+      const VR sx = VR((g5 && row >= (n >> 1)) ? -1 : 1);
+      o.re += sx * xv.re;
+      o.im += sx * xv.im;
     }
+    if (g5 && row >= (n >> 1)) o = mk(-o.re, -o.im);
     reduced_epilogue<EPI>(i, o, out, e, y, c0, ca, cb);
   } else {
     if (x_e) {
       const int item = 5 * x;
       R.load_stream(block_ptr<T, P>(blocks, size_t(item)), lane);
       const A s = (P == P16S) ? A(scales[item]) : A(1);
-      wave_product<T, P, FULL, 0>(R, s, x_e + size_t(r) * n, self_part, n, tm, lane);
+      wave_product<T, P, FULL, 0>(R, s, x_e + size_t(r) * n, self_part, n, tm, lane, g5 & 1);
     } else {
       self_part[lane] = mk(VR(0), VR(0));
     }
@@ -985,6 +1042,7 @@ __global__ __launch_bounds__(64) void k_reduced_gather(
       o.re += -h[k].re;
       o.im += -h[k].im;
     }
+    if (g5 && lane >= (n >> 1)) o = mk(-o.re, -o.im);
     reduced_epilogue<EPI>(size_t(r) * n + lane, o, out, e, y, c0, ca, cb);
   }
 }
@@ -1257,15 +1315,27 @@ void launch_neighbours(int* nbr, int L0, int L1, int L2, int L3, hipStream_t st)
   DC_HIP(hipGetLastError());
 }
 
+// bytes per complex block entry
+constexpr size_t block_entry(int p) { return p == P64 ? 16 : p == P32 ? 8 : 4; }
+
+// Blocks beyond the 256 MB last-level cache are loaded non-temporally: a pass
+// evicts them before the next one comes, and past the caches they leave those to the
+// slots.  Within it a repeated apply finds them there, unless the loads say that
+// they are not reused (one apply, cached / non-temporal, us; n = 48 but for the first):
+// 80 MB FP64 n = 16 18.9 / 21.1, 180 MB FP16 36.2 / 42.5, 360 MB FP32 78.5 / 68.4,
+// 720 MB FP64 157 / 141, 2.9 GB FP16 659 / 626, 5.8 GB FP32 1202 / 1084.
+constexpr size_t kCacheBytes = size_t(256) << 20;
+
 template <int P>
 static void apply_T(int n, int V, const void* blocks, const float* scales, const void* in,
                     void* gbuf, const int* nbr, double tm, const int* done, hipStream_t st,
-                    hipEvent_t ev0, hipEvent_t ev1) {
+                    hipEvent_t ev0, hipEvent_t ev1, int g5) {
   using VR = typename VecOf<P>::R;
   const int chunk = (5 * V + 7) / 8;
   const dim3 grid(unsigned(chunk) * 8u), block(64);
   const auto* pin = static_cast<const cx<VR>*>(in);
   auto* pg = static_cast<cx<VR>*>(gbuf);
+  const int stream = size_t(V) * 5 * n * n * block_entry(P) > kCacheBytes;
   const bool full = (n % 8) == 0;
   switch (tile_T(n)) {
   // with events: the dispatch itself records its start and end (no marker packets)
@@ -1273,10 +1343,10 @@ static void apply_T(int n, int V, const void* blocks, const float* scales, const
   case TV:                                                                                    \
     if (full)                                                                                 \
       hipExtLaunchKernelGGL((k_apply_blocks<TV, P, true>), grid, block, 0, st, ev0, ev1, 0,   \
-                            blocks, scales, pin, pg, nbr, V, n, chunk, tm, done);            \
+                            blocks, scales, pin, pg, nbr, V, n, chunk, tm, g5, stream, done);    \
     else                                                                                      \
       hipExtLaunchKernelGGL((k_apply_blocks<TV, P, false>), grid, block, 0, st, ev0, ev1, 0,  \
-                            blocks, scales, pin, pg, nbr, V, n, chunk, tm, done);            \
+                            blocks, scales, pin, pg, nbr, V, n, chunk, tm, g5, stream, done);    \
     break;
     DC_CASE(1) DC_CASE(2) DC_CASE(3) DC_CASE(4) DC_CASE(5) DC_CASE(6) DC_CASE(7) DC_CASE(8)
 #undef DC_CASE
@@ -1288,10 +1358,66 @@ static void apply_T(int n, int V, const void* blocks, const float* scales, const
 
 void launch_apply_blocks(Prec p, int n, int V, const void* blocks, const float* scales,
                          const void* in, void* gbuf, const int* nbr, double tm, const int* done,
-                         hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-  if (p == P64) apply_T<P64>(n, V, blocks, scales, in, gbuf, nbr, tm, done, st, ev0, ev1);
-  else if (p == P32) apply_T<P32>(n, V, blocks, scales, in, gbuf, nbr, tm, done, st, ev0, ev1);
-  else apply_T<P16S>(n, V, blocks, scales, in, gbuf, nbr, tm, done, st, ev0, ev1);
+                         hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, int g5) {
+  if (p == P64) apply_T<P64>(n, V, blocks, scales, in, gbuf, nbr, tm, done, st, ev0, ev1, g5);
+  else if (p == P32) apply_T<P32>(n, V, blocks, scales, in, gbuf, nbr, tm, done, st, ev0, ev1, g5);
+  else apply_T<P16S>(n, V, blocks, scales, in, gbuf, nbr, tm, done, st, ev0, ev1, g5);
+}
+
+// The one-launch form reads every hop block twice: it is the faster one while that
+// costs less than a second launch and the slots' way through the caches, so up to
+// the eight 4 MB L2s (one apply, two launches / one, us): 5 MB FP64 11.1 / 8.6, 20 MB
+// FP16 11.1 / 8.7, 28 MB FP32 11.0 / 8.5; 40 MB FP64 11.7 / 12.4, 57 MB FP64 14.0 / 15.4.
+constexpr size_t kSiteBytes = size_t(32) << 20;
+
+// Tiles it takes: FP64 tiles of T >= 6 would spill (nine waves: 168 registers each).
+template <int P>
+constexpr bool site_tile(int T) { return T >= 1 && T <= (P == P64 ? 5 : 8); }
+
+bool apply_one_launch(Prec p, int n, int V) {
+  if (p == P64 && !site_tile<P64>(tile_T(n))) return false;
+  return size_t(V) * 5 * n * n * block_entry(p) <= kSiteBytes;
+}
+
+template <int P>
+static void site_T(int n, int V, const void* blocks, const float* scales, const void* in, void* out,
+                   const int* nbr, double tm, const int* done, hipStream_t st, hipEvent_t ev0,
+                   hipEvent_t ev1, int g5) {
+  using VR = typename VecOf<P>::R;
+  const int chunk = (V + 7) / 8;
+  const dim3 grid(unsigned(chunk) * 8u), block(64 * kRedWaves);
+  const auto* pin = static_cast<const cx<VR>*>(in);
+  auto* po = static_cast<cx<VR>*>(out);
+  const bool full = (n % 8) == 0;
+  const int g = g5 ? 3 : 0;
+  switch (tile_T(n)) {
+#define DC_CASE(TV)                                                                          \
+  case TV:                                                                                   \
+    if constexpr (site_tile<P>(TV)) {                                                        \
+      if (full)                                                                              \
+        hipExtLaunchKernelGGL((k_apply_site<TV, P, true>), grid, block, 0, st, ev0, ev1, 0,  \
+                              blocks, scales, pin, po, nbr, V, n, chunk, tm, g, done);       \
+      else                                                                                   \
+        hipExtLaunchKernelGGL((k_apply_site<TV, P, false>), grid, block, 0, st, ev0, ev1, 0, \
+                              blocks, scales, pin, po, nbr, V, n, chunk, tm, g, done);       \
+    }                                                                                        \
+    break;
+    DC_CASE(1) DC_CASE(2) DC_CASE(3) DC_CASE(4) DC_CASE(5) DC_CASE(6) DC_CASE(7) DC_CASE(8)
+#undef DC_CASE
+    default:
+      throw InvalidArg("block size n > 64 is not supported");
+  }
+  DC_HIP(hipGetLastError());
+}
+
+void launch_apply_site(Prec p, int n, int V, const void* blocks, const float* scales, const void* in,
+                       void* out, const int* nbr, double tm, const int* done, hipStream_t st,
+                       hipEvent_t ev0, hipEvent_t ev1, int g5) {
+  if (p == P64 && !site_tile<P64>(tile_T(n)))
+    throw InvalidArg("the one-launch apply does not take this block size in FP64");
+  if (p == P64) site_T<P64>(n, V, blocks, scales, in, out, nbr, tm, done, st, ev0, ev1, g5);
+  else if (p == P32) site_T<P32>(n, V, blocks, scales, in, out, nbr, tm, done, st, ev0, ev1, g5);
+  else site_T<P16S>(n, V, blocks, scales, in, out, nbr, tm, done, st, ev0, ev1, g5);
 }
 
 template <int P, bool FROMBUF, int EPI>
@@ -1355,7 +1481,7 @@ template <int P>
 static void reduced_oe_T(int n, int V, const void* blocks, const float* scales, const void* inv,
                          const float* invsc, const void* x_e, void* t_o, const int* nbr,
                          const int* osite, const int* done, hipStream_t st, hipEvent_t ev0,
-                         hipEvent_t ev1) {
+                         hipEvent_t ev1, int g5) {
   using VR = typename VecOf<P>::R;
   const int rows = V / 2;
   const int chunk = (rows + 7) / 8;
@@ -1368,10 +1494,10 @@ static void reduced_oe_T(int n, int V, const void* blocks, const float* scales, 
   case TV:                                                                                    \
     if (full)                                                                                 \
       hipExtLaunchKernelGGL((k_reduced_oe<TV, P, true>), grid, block, 0, st, ev0, ev1, 0,     \
-                            blocks, scales, inv, invsc, xe, to, nbr, osite, V, n, chunk, done); \
+                            blocks, scales, inv, invsc, xe, to, nbr, osite, V, n, chunk, g5, done); \
     else                                                                                      \
       hipExtLaunchKernelGGL((k_reduced_oe<TV, P, false>), grid, block, 0, st, ev0, ev1, 0,    \
-                            blocks, scales, inv, invsc, xe, to, nbr, osite, V, n, chunk, done); \
+                            blocks, scales, inv, invsc, xe, to, nbr, osite, V, n, chunk, g5, done); \
     break;
     DC_CASE(1) DC_CASE(2) DC_CASE(3) DC_CASE(4) DC_CASE(5) DC_CASE(6) DC_CASE(7) DC_CASE(8)
 #undef DC_CASE
@@ -1384,11 +1510,11 @@ static void reduced_oe_T(int n, int V, const void* blocks, const float* scales, 
 void launch_reduced_oe(Prec p, int n, int V, const void* blocks, const float* scales,
                        const void* inv, const float* invsc, const void* x_e, void* t_o,
                        const int* nbr, const int* osite, const int* done, hipStream_t st,
-                       hipEvent_t ev0, hipEvent_t ev1) {
+                       hipEvent_t ev0, hipEvent_t ev1, int g5) {
   if (V < 2 || V % 2) throw InvalidArg("the reduced operator needs an even number of sites");
-  if (p == P64) reduced_oe_T<P64>(n, V, blocks, scales, inv, invsc, x_e, t_o, nbr, osite, done, st, ev0, ev1);
-  else if (p == P32) reduced_oe_T<P32>(n, V, blocks, scales, inv, invsc, x_e, t_o, nbr, osite, done, st, ev0, ev1);
-  else reduced_oe_T<P16S>(n, V, blocks, scales, inv, invsc, x_e, t_o, nbr, osite, done, st, ev0, ev1);
+  if (p == P64) reduced_oe_T<P64>(n, V, blocks, scales, inv, invsc, x_e, t_o, nbr, osite, done, st, ev0, ev1, g5);
+  else if (p == P32) reduced_oe_T<P32>(n, V, blocks, scales, inv, invsc, x_e, t_o, nbr, osite, done, st, ev0, ev1, g5);
+  else reduced_oe_T<P16S>(n, V, blocks, scales, inv, invsc, x_e, t_o, nbr, osite, done, st, ev0, ev1, g5);
 }
 
 template <int P, int EPI, bool BJ>
@@ -1396,7 +1522,7 @@ static void reduced_eo_T(int n, int V, const void* blocks, const float* scales, 
                          const float* einvsc, const void* x_e, const void* t_o, const int* nbr,
                          const int* esite, double tm, void* out, const void* e, void* y, z64 c0,
                          z64 ca, z64 cb, const int* done, hipStream_t st, hipEvent_t ev0,
-                         hipEvent_t ev1) {
+                         hipEvent_t ev1, int g5) {
   using VR = typename VecOf<P>::R;
   const int rows = V / 2;
   const int chunk = (rows + 7) / 8;
@@ -1413,11 +1539,11 @@ static void reduced_eo_T(int n, int V, const void* blocks, const float* scales, 
     if (full)                                                                                    \
       hipExtLaunchKernelGGL((k_reduced_eo<TV, P, true, EPI, BJ>), grid, block, 0, st, ev0, ev1,  \
                             0, blocks, scales, einv, einvsc, xe, to, nbr, esite, V, n, chunk, tm, \
-                            o, ee, yy, c0, ca, cb, done);                                        \
+                            o, ee, yy, c0, ca, cb, g5, done);                                        \
     else                                                                                         \
       hipExtLaunchKernelGGL((k_reduced_eo<TV, P, false, EPI, BJ>), grid, block, 0, st, ev0, ev1, \
                             0, blocks, scales, einv, einvsc, xe, to, nbr, esite, V, n, chunk, tm, \
-                            o, ee, yy, c0, ca, cb, done);                                        \
+                            o, ee, yy, c0, ca, cb, g5, done);                                        \
     break;
     DC_CASE(1) DC_CASE(2) DC_CASE(3) DC_CASE(4) DC_CASE(5) DC_CASE(6) DC_CASE(7) DC_CASE(8)
 #undef DC_CASE
@@ -1432,8 +1558,8 @@ static void reduced_eo_P(int epi, int n, int V, const void* blocks, const float*
                          const void* einv, const float* einvsc, const void* x_e, const void* t_o,
                          const int* nbr, const int* esite, double tm, void* out, const void* e,
                          void* y, z64 c0, z64 ca, z64 cb, const int* done, hipStream_t st,
-                         hipEvent_t ev0, hipEvent_t ev1) {
-#define DC_ARGS n, V, blocks, scales, einv, einvsc, x_e, t_o, nbr, esite, tm, out, e, y, c0, ca, cb, done, st, ev0, ev1
+                         hipEvent_t ev0, hipEvent_t ev1, int g5) {
+#define DC_ARGS n, V, blocks, scales, einv, einvsc, x_e, t_o, nbr, esite, tm, out, e, y, c0, ca, cb, done, st, ev0, ev1, g5
   if (einv) {
     switch (epi) {
       case 0: reduced_eo_T<P, 0, true>(DC_ARGS); break;
@@ -1455,7 +1581,7 @@ void launch_reduced_eo(Prec p, int epi, int n, int V, const void* blocks, const 
                        const void* einv, const float* einvsc, const void* x_e, const void* t_o,
                        const int* nbr, const int* esite, double tm, void* out, const void* e,
                        void* y, z64 c0, z64 ca, z64 cb, const int* done, hipStream_t st,
-                       hipEvent_t ev0, hipEvent_t ev1) {
+                       hipEvent_t ev0, hipEvent_t ev1, int g5) {
   if (epi < 0 || epi > 3) throw InvalidArg("reduced epilogue must be 0..3");
   if (einv && epi == 3) throw InvalidArg("the residual epilogue takes the unpreconditioned operator");
   if (einv && p == P16S && !einvsc) throw InvalidArg("FP16 inverses need their scales");
@@ -1463,7 +1589,7 @@ void launch_reduced_eo(Prec p, int epi, int n, int V, const void* blocks, const 
   if (!t_o || !out) throw InvalidArg("null vector pointer");
   if ((epi == 1 || epi == 3) && !e) throw InvalidArg("null epilogue input");
   if ((epi == 1 || epi == 2) && !y) throw InvalidArg("null chain output");
-#define DC_ARGS epi, n, V, blocks, scales, einv, einvsc, x_e, t_o, nbr, esite, tm, out, e, y, c0, ca, cb, done, st, ev0, ev1
+#define DC_ARGS epi, n, V, blocks, scales, einv, einvsc, x_e, t_o, nbr, esite, tm, out, e, y, c0, ca, cb, done, st, ev0, ev1, g5
   if (p == P64) reduced_eo_P<P64>(DC_ARGS);
   else if (p == P32) reduced_eo_P<P32>(DC_ARGS);
   else reduced_eo_P<P16S>(DC_ARGS);
@@ -1507,7 +1633,7 @@ template <int P>
 static void reduced_scatter_T(int n, int V, const void* blocks, const float* scales,
                               const void* inv, const float* invsc, const void* x_e, void* hp,
                               const int* nbr, const int* osite, const int* done, hipStream_t st,
-                              hipEvent_t ev0, hipEvent_t ev1) {
+                              hipEvent_t ev0, hipEvent_t ev1, int g5) {
   using VR = typename VecOf<P>::R;
   const int rows = V / 2;
   const int chunk = (rows + 7) / 8;
@@ -1522,11 +1648,11 @@ static void reduced_scatter_T(int n, int V, const void* blocks, const float* sca
       if (full)                                                                                \
         hipExtLaunchKernelGGL((k_reduced_scatter<TV, P, true>), grid, block, 0, st, ev0, ev1,  \
                               0, blocks, scales, inv, invsc, xe, h, nbr, osite, V, n, chunk,   \
-                              done);                                                           \
+                              g5, done);                                                           \
       else                                                                                     \
         hipExtLaunchKernelGGL((k_reduced_scatter<TV, P, false>), grid, block, 0, st, ev0, ev1, \
                               0, blocks, scales, inv, invsc, xe, h, nbr, osite, V, n, chunk,   \
-                              done);                                                           \
+                              g5, done);                                                           \
     }                                                                                          \
     break;
     DC_CASE(1) DC_CASE(2) DC_CASE(3) DC_CASE(4) DC_CASE(5) DC_CASE(6) DC_CASE(7) DC_CASE(8)
@@ -1540,15 +1666,15 @@ static void reduced_scatter_T(int n, int V, const void* blocks, const float* sca
 void launch_reduced_scatter(Prec p, int n, int V, const void* blocks, const float* scales,
                             const void* inv, const float* invsc, const void* x_e, void* hp,
                             const int* nbr, const int* osite, const int* done, hipStream_t st,
-                            hipEvent_t ev0, hipEvent_t ev1) {
+                            hipEvent_t ev0, hipEvent_t ev1, int g5) {
   if (V < 2 || V % 2) throw InvalidArg("the reduced operator needs an even number of sites");
   if (!single_read_fits(p, n))
     throw InvalidArg("the single-read reduced kernels do not take this precision and block size");
   if (p == P16S && (!scales || !invsc)) throw InvalidArg("FP16 blocks need their scales");
   if (!x_e || !hp || !inv) throw InvalidArg("null pointer");
-  if (p == P64) reduced_scatter_T<P64>(n, V, blocks, scales, inv, invsc, x_e, hp, nbr, osite, done, st, ev0, ev1);
-  else if (p == P32) reduced_scatter_T<P32>(n, V, blocks, scales, inv, invsc, x_e, hp, nbr, osite, done, st, ev0, ev1);
-  else reduced_scatter_T<P16S>(n, V, blocks, scales, inv, invsc, x_e, hp, nbr, osite, done, st, ev0, ev1);
+  if (p == P64) reduced_scatter_T<P64>(n, V, blocks, scales, inv, invsc, x_e, hp, nbr, osite, done, st, ev0, ev1, g5);
+  else if (p == P32) reduced_scatter_T<P32>(n, V, blocks, scales, inv, invsc, x_e, hp, nbr, osite, done, st, ev0, ev1, g5);
+  else reduced_scatter_T<P16S>(n, V, blocks, scales, inv, invsc, x_e, hp, nbr, osite, done, st, ev0, ev1, g5);
 }
 
 template <int P, int EPI, bool BJ>
@@ -1556,7 +1682,7 @@ static void reduced_gather_T(int n, int V, const void* blocks, const float* scal
                              const void* einv, const float* einvsc, const void* x_e,
                              const void* hp, const int* esite, double tm, void* out,
                              const void* e, void* y, z64 c0, z64 ca, z64 cb, const int* done,
-                             hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+                             hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, int g5) {
   using VR = typename VecOf<P>::R;
   const int rows = V / 2;
   const int chunk = (rows + 7) / 8;
@@ -1574,11 +1700,11 @@ static void reduced_gather_T(int n, int V, const void* blocks, const float* scal
       if (full)                                                                                 \
         hipExtLaunchKernelGGL((k_reduced_gather<TV, P, true, EPI, BJ>), grid, block, 0, st,     \
                               ev0, ev1, 0, blocks, scales, einv, einvsc, xe, h, esite, V, n,    \
-                              chunk, tm, o, ee, yy, c0, ca, cb, done);                          \
+                              chunk, tm, o, ee, yy, c0, ca, cb, g5, done);                          \
       else                                                                                      \
         hipExtLaunchKernelGGL((k_reduced_gather<TV, P, false, EPI, BJ>), grid, block, 0, st,    \
                               ev0, ev1, 0, blocks, scales, einv, einvsc, xe, h, esite, V, n,    \
-                              chunk, tm, o, ee, yy, c0, ca, cb, done);                          \
+                              chunk, tm, o, ee, yy, c0, ca, cb, g5, done);                          \
     }                                                                                           \
     break;
     DC_CASE(1) DC_CASE(2) DC_CASE(3) DC_CASE(4) DC_CASE(5) DC_CASE(6) DC_CASE(7) DC_CASE(8)
@@ -1594,8 +1720,8 @@ static void reduced_gather_P(int epi, int n, int V, const void* blocks, const fl
                              const void* einv, const float* einvsc, const void* x_e,
                              const void* hp, const int* esite, double tm, void* out,
                              const void* e, void* y, z64 c0, z64 ca, z64 cb, const int* done,
-                             hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-#define DC_ARGS n, V, blocks, scales, einv, einvsc, x_e, hp, esite, tm, out, e, y, c0, ca, cb, done, st, ev0, ev1
+                             hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, int g5) {
+#define DC_ARGS n, V, blocks, scales, einv, einvsc, x_e, hp, esite, tm, out, e, y, c0, ca, cb, done, st, ev0, ev1, g5
   if (einv) {
     switch (epi) {
       case 0: reduced_gather_T<P, 0, true>(DC_ARGS); break;
@@ -1617,7 +1743,7 @@ void launch_reduced_gather(Prec p, int epi, int n, int V, const void* blocks,
                            const float* scales, const void* einv, const float* einvsc,
                            const void* x_e, const void* hp, const int* esite, double tm,
                            void* out, const void* e, void* y, z64 c0, z64 ca, z64 cb,
-                           const int* done, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+                           const int* done, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, int g5) {
   if (epi < 0 || epi > 3) throw InvalidArg("reduced epilogue must be 0..3");
   if (einv && epi == 3) throw InvalidArg("the residual epilogue takes the unpreconditioned operator");
   if (!single_read_fits(p, n))
@@ -1629,7 +1755,7 @@ void launch_reduced_gather(Prec p, int epi, int n, int V, const void* blocks,
   if (einv && !x_e) throw InvalidArg("block Jacobi needs x_e");
   if ((epi == 1 || epi == 3) && !e) throw InvalidArg("null epilogue input");
   if ((epi == 1 || epi == 2) && !y) throw InvalidArg("null chain output");
-#define DC_ARGS epi, n, V, blocks, scales, einv, einvsc, x_e, hp, esite, tm, out, e, y, c0, ca, cb, done, st, ev0, ev1
+#define DC_ARGS epi, n, V, blocks, scales, einv, einvsc, x_e, hp, esite, tm, out, e, y, c0, ca, cb, done, st, ev0, ev1, g5
   if (p == P64) reduced_gather_P<P64>(DC_ARGS);
   else if (p == P32) reduced_gather_P<P32>(DC_ARGS);
   else reduced_gather_P<P16S>(DC_ARGS);

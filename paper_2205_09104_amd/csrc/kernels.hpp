@@ -45,10 +45,17 @@ void launch_neighbours(int* nbr, int L0, int L1, int L2, int L3, hipStream_t st)
 // Gamma5 B^H Gamma5 psi_x into slot mu of gbuf[x+mu].  gbuf: [V][9][n] in the
 // vector precision.
 // ev0/ev1 (optional): events that the dispatch records at its start and end.
+// g5: Gamma5 D Gamma5 instead of D (with tm = -mu: the adjoint).
 void launch_apply_blocks(Prec p, int n, int V, const void* blocks, const float* scales,
                          const void* in, void* gbuf, const int* nbr, double tm,
                          const int* done, hipStream_t st, hipEvent_t ev0 = nullptr,
-                         hipEvent_t ev1 = nullptr);
+                         hipEvent_t ev1 = nullptr, int g5 = 0);
+// The whole apply in one launch, out = D in (out not overlapping in; the same sums,
+// equal bit for bit), and whether an operator of this size takes it.
+void launch_apply_site(Prec p, int n, int V, const void* blocks, const float* scales, const void* in,
+                       void* out, const int* nbr, double tm, const int* done, hipStream_t st,
+                       hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, int g5 = 0);
+bool apply_one_launch(Prec p, int n, int V);
 
 // Apply, stage 2 (sum of the 9 slots in a fixed order) with an epilogue.
 //   store : out = s
@@ -92,13 +99,14 @@ void launch_bj_rows(Prec p, int n, int rows, const int* rowsite, const void* inv
 // ---------------------------------------------------------------- odd-even reduction
 // The reduced operator S = A_e - D_eo A_o^{-1} D_oe over compressed vectors
 // (site x of a parity at row x / 2, every extent even), two site-centric kernels.
+// g5 (each of them): Gamma5 before the first and after the second (epilogue 0).
 // launch_reduced_oe: t_o = A_o^{-1} D_oe x_e, with inv / invsc the self-block
 // inverses of every site (tiled, indexed by site) and osite: int32 [V/2] odd
 // row -> site.
 void launch_reduced_oe(Prec p, int n, int V, const void* blocks, const float* scales,
                        const void* inv, const float* invsc, const void* x_e, void* t_o,
                        const int* nbr, const int* osite, const int* done, hipStream_t st,
-                       hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+                       hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, int g5 = 0);
 // launch_reduced_eo: s = A_e x_e - D_eo t_o (x_e null: -D_eo t_o) with the
 // epilogue epi: 0 out = s; 1 p = e - ca s, out = p, y = c0 e + cb p; 2 p = out -
 // ca s, out = p, y += cb p; 3 out = e - s.  esite: int32 [V/2] even row -> site.
@@ -109,7 +117,7 @@ void launch_reduced_eo(Prec p, int epi, int n, int V, const void* blocks, const 
                        const void* einv, const float* einvsc, const void* x_e, const void* t_o,
                        const int* nbr, const int* esite, double tm, void* out, const void* e,
                        void* y, z64 c0, z64 ca, z64 cb, const int* done, hipStream_t st,
-                       hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+                       hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, int g5 = 0);
 // Single-read form of the same operator (FP32 / FP16 blocks, FP64 blocks up to
 // n = 48): launch_reduced_scatter forms t_o as launch_reduced_oe does and,
 // from the same read of each hop block, the eight D_eo products of t_o that each
@@ -120,13 +128,13 @@ void launch_reduced_eo(Prec p, int epi, int n, int V, const void* blocks, const 
 void launch_reduced_scatter(Prec p, int n, int V, const void* blocks, const float* scales,
                             const void* inv, const float* invsc, const void* x_e, void* hp,
                             const int* nbr, const int* osite, const int* done, hipStream_t st,
-                            hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+                            hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, int g5 = 0);
 void launch_reduced_gather(Prec p, int epi, int n, int V, const void* blocks,
                            const float* scales, const void* einv, const float* einvsc,
                            const void* x_e, const void* hp, const int* esite, double tm,
                            void* out, const void* e, void* y, z64 c0, z64 ca, z64 cb,
                            const int* done, hipStream_t st, hipEvent_t ev0 = nullptr,
-                           hipEvent_t ev1 = nullptr);
+                           hipEvent_t ev1 = nullptr, int g5 = 0);
 // Which form the solver's reduced applies take (process-wide): mode 0
 // (default) the single-read pair where it applies (reduced_single_read), 1
 // always the two-kernel form.

@@ -456,7 +456,7 @@ CycleSignal::~CycleSignal() {
 // accumulated, so the event pool stays small.
 static void stage1(Op& op, Prec p, int n, int V, const void* blocks, const float* scales,
                    const void* in, void* gbuf, const int* nbr, double tm, const int* done,
-                   hipStream_t st) {
+                   hipStream_t st, int g5 = 0) {
   ApplyProfile& pr = op.prof;
   hipEvent_t a = nullptr, b = nullptr;
   const int slot = prec_slot(p);
@@ -464,14 +464,36 @@ static void stage1(Op& op, Prec p, int n, int V, const void* blocks, const float
     if (pr.tag < 0 && pr.recs.size() >= 2048) pr.flush();
     if (!pr.take(&a, &b)) ++pr.missed;
   }
-  launch_apply_blocks(p, n, V, blocks, scales, in, gbuf, nbr, tm, done, st, a, b);
+  launch_apply_blocks(p, n, V, blocks, scales, in, gbuf, nbr, tm, done, st, a, b, g5);
+  if (a) pr.recs.push_back({a, b, slot, done ? pr.tag : -1, false, 1});
+}
+
+// out = D in (g5: Gamma5 D Gamma5 in), one_launch: in a single launch (in and out
+// must not overlap), timed in stage 1's slot, else stage 1 into gbuf and its gather.
+static void apply_store(Op& op, Prec p, bool one_launch, const void* in, void* gbuf, void* out,
+                        double tm, const int* done, hipStream_t st, int g5 = 0) {
+  if (!one_launch) {
+    stage1(op, p, op.n, op.V, op.blocks(p), op.scales(p), in, gbuf, op.nbr.as<int>(), tm, done, st,
+           g5);
+    launch_gather_store(p, op.n, op.V, gbuf, out, done, st);
+    return;
+  }
+  ApplyProfile& pr = op.prof;
+  hipEvent_t a = nullptr, b = nullptr;
+  const int slot = prec_slot(p);
+  if (pr.sample(slot)) {
+    if (pr.tag < 0 && pr.recs.size() >= 2048) pr.flush();
+    if (!pr.take(&a, &b)) ++pr.missed;
+  }
+  launch_apply_site(p, op.n, op.V, op.blocks(p), op.scales(p), in, out, op.nbr.as<int>(), tm, done, st,
+                    a, b, g5);
   if (a) pr.recs.push_back({a, b, slot, done ? pr.tag : -1, false, 1});
 }
 
 // The reduced operator's kernels (Sec. 2.2, factored form), timed like stage1:
 // t_o = A_o^{-1} D_oe x_e, then A_e x_e - D_eo t_o with an epilogue.
 static void reduced_oe(Op& op, Prec p, const void* inv, const float* invsc, const void* x_e,
-                       void* t_o, const int* done, hipStream_t st) {
+                       void* t_o, const int* done, hipStream_t st, int g5 = 0) {
   ApplyProfile& pr = op.prof;
   hipEvent_t a = nullptr, b = nullptr;
   const int slot = 3 + prec_slot(p);
@@ -480,13 +502,13 @@ static void reduced_oe(Op& op, Prec p, const void* inv, const float* invsc, cons
     if (!pr.take(&a, &b)) ++pr.missed;
   }
   launch_reduced_oe(p, op.n, op.V, op.blocks(p), op.scales(p), inv, invsc, x_e, t_o,
-                    op.nbr.as<int>(), op.osite.as<int>(), done, st, a, b);
+                    op.nbr.as<int>(), op.osite.as<int>(), done, st, a, b, g5);
   if (a) pr.recs.push_back({a, b, slot, done ? pr.tag : -1, false, 2});
 }
 
 static void reduced_eo(Op& op, Prec p, int epi, const void* einv, const float* einvsc,
                        const void* x_e, const void* t_o, double tm, void* out, const void* e,
-                       void* y, z64 c0, z64 ca, z64 cb, const int* done, hipStream_t st) {
+                       void* y, z64 c0, z64 ca, z64 cb, const int* done, hipStream_t st, int g5 = 0) {
   ApplyProfile& pr = op.prof;
   hipEvent_t a = nullptr, b = nullptr;
   const int slot = 6 + prec_slot(p);
@@ -495,7 +517,7 @@ static void reduced_eo(Op& op, Prec p, int epi, const void* einv, const float* e
     if (!pr.take(&a, &b)) ++pr.missed;
   }
   launch_reduced_eo(p, epi, op.n, op.V, op.blocks(p), op.scales(p), einv, einvsc, x_e, t_o,
-                    op.nbr.as<int>(), op.esite.as<int>(), tm, out, e, y, c0, ca, cb, done, st, a, b);
+                    op.nbr.as<int>(), op.esite.as<int>(), tm, out, e, y, c0, ca, cb, done, st, a, b, g5);
   if (a) {
     // distinct vectors read (x_e, t_o and the epilogue's inputs) plus writes
     int passes = 1 + (x_e ? 1 : 0);
@@ -511,7 +533,7 @@ static void reduced_eo(Op& op, Prec p, int epi, const void* einv, const float* e
 // the full-lattice apply's partial buffer (V x 9 x n vectors, at least the
 // V/2 x 8 x n the pair needs); the two uses never overlap on the stream.
 static void reduced_scatter(Op& op, Prec p, const void* inv, const float* invsc,
-                            const void* x_e, void* hp, const int* done, hipStream_t st) {
+                            const void* x_e, void* hp, const int* done, hipStream_t st, int g5 = 0) {
   ApplyProfile& pr = op.prof;
   hipEvent_t a = nullptr, b = nullptr;
   const int slot = 3 + prec_slot(p);
@@ -520,14 +542,14 @@ static void reduced_scatter(Op& op, Prec p, const void* inv, const float* invsc,
     if (!pr.take(&a, &b)) ++pr.missed;
   }
   launch_reduced_scatter(p, op.n, op.V, op.blocks(p), op.scales(p), inv, invsc, x_e, hp,
-                         op.nbr.as<int>(), op.osite.as<int>(), done, st, a, b);
+                         op.nbr.as<int>(), op.osite.as<int>(), done, st, a, b, g5);
   // x_e read once, eight partial vectors written
   if (a) pr.recs.push_back({a, b, slot, done ? pr.tag : -1, false, 9});
 }
 
 static void reduced_gather(Op& op, Prec p, int epi, const void* einv, const float* einvsc,
                            const void* x_e, const void* hp, double tm, void* out, const void* e,
-                           void* y, z64 c0, z64 ca, z64 cb, const int* done, hipStream_t st) {
+                           void* y, z64 c0, z64 ca, z64 cb, const int* done, hipStream_t st, int g5 = 0) {
   ApplyProfile& pr = op.prof;
   hipEvent_t a = nullptr, b = nullptr;
   const int slot = 6 + prec_slot(p);
@@ -536,7 +558,7 @@ static void reduced_gather(Op& op, Prec p, int epi, const void* einv, const floa
     if (!pr.take(&a, &b)) ++pr.missed;
   }
   launch_reduced_gather(p, epi, op.n, op.V, op.blocks(p), op.scales(p), einv, einvsc, x_e, hp,
-                        op.esite.as<int>(), tm, out, e, y, c0, ca, cb, done, st, a, b);
+                        op.esite.as<int>(), tm, out, e, y, c0, ca, cb, done, st, a, b, g5);
   if (a) {
     // the eight partial vectors, x_e, the epilogue's inputs, and the writes
     int passes = 8 + (x_e ? 1 : 0);
@@ -578,18 +600,12 @@ void op_apply(Op& op, Prec p, int adjoint, const void* in, void* out, hipStream_
   check_prec(op, p);
   if (!in || !out) throw InvalidArg("null vector pointer");
   if (in == out) throw InvalidArg("in and out must not overlap");
-  if (!adjoint) {
-    stage1(op, p, op.n, op.V, op.blocks(p), op.scales(p), in, op.gbuf(p), op.nbr.as<int>(),
-                        op.mu, nullptr, st);
-    launch_gather_store(p, op.n, op.V, op.gbuf(p), out, nullptr, st);
-  } else {
-    // D(mu)^H = Gamma5 D(-mu) Gamma5
-    launch_gamma5(p, in, out, op.V, op.n, st);
-    stage1(op, p, op.n, op.V, op.blocks(p), op.scales(p), out, op.gbuf(p),
-                        op.nbr.as<int>(), -op.mu, nullptr, st);
-    launch_gather_store(p, op.n, op.V, op.gbuf(p), out, nullptr, st);
-    launch_gamma5(p, out, out, op.V, op.n, st);
-  }
+  const size_t span = op.N() * vec_bytes(p);
+  const char *a = static_cast<const char*>(in), *b = static_cast<const char*>(out);
+  const bool apart = a + span <= b || b + span <= a;
+  // D(mu)^H = Gamma5 D(-mu) Gamma5
+  apply_store(op, p, apart && apply_one_launch(p, op.n, op.V), in, op.gbuf(p), out,
+              adjoint ? -op.mu : op.mu, nullptr, st, adjoint);
 }
 
 const Op::BJ& Op::ensure_bj(int sign, hipStream_t st) {
@@ -642,23 +658,18 @@ void op_apply_reduced(Op& op, Prec p, int adjoint, int block_jacobi, const void*
   const void* bj_e = block_jacobi ? inv : nullptr;
   const float* bj_esc = block_jacobi ? invsc : nullptr;
   void* ts = op.tmp_s(p);
-  const void* src = in;
-  if (adjoint) {
-    launch_gamma5(p, in, out, half, op.n, st);
-    src = out;
-  }
   const z64 z = mk(0.0, 0.0);
+  // the second kernel reads in only on its own row before writing that row of out
   if (reduced_single_read(p, op.n, op.V)) {
     void* hp = op.gbuf(p);
-    reduced_scatter(op, p, inv, invsc, src, hp, nullptr, st);
-    reduced_gather(op, p, 0, bj_e, bj_esc, src, hp, tm, out, nullptr, nullptr, z, z, z, nullptr,
-                   st);
+    reduced_scatter(op, p, inv, invsc, in, hp, nullptr, st, adjoint);
+    reduced_gather(op, p, 0, bj_e, bj_esc, in, hp, tm, out, nullptr, nullptr, z, z, z, nullptr, st,
+                   adjoint);
   } else {
-    reduced_oe(op, p, inv, invsc, src, ts, nullptr, st);
-    // the D_eo kernel reads src only on its own row before writing that row of out
-    reduced_eo(op, p, 0, bj_e, bj_esc, src, ts, tm, out, nullptr, nullptr, z, z, z, nullptr, st);
+    reduced_oe(op, p, inv, invsc, in, ts, nullptr, st, adjoint);
+    reduced_eo(op, p, 0, bj_e, bj_esc, in, ts, tm, out, nullptr, nullptr, z, z, z, nullptr, st,
+               adjoint);
   }
-  if (adjoint) launch_gamma5(p, out, out, half, op.n, st);
 }
 
 void op_apply_reduced_noalloc(Op& op, Prec p, int adjoint, const void* in, void* out,
@@ -688,18 +699,12 @@ void op_apply_reduced_noalloc(Op& op, Prec p, int adjoint, const void* in, void*
   const void* inv = bj_blocks(bj, p);
   const float* invsc = (p == P16S) ? bj.sc16.as<float>() : nullptr;
   const double tm = sign * op.mu;
-  const void* src = in;
-  if (adjoint) {
-    launch_gamma5(p, in, out, half, op.n, st);
-    src = out;
-  }
   const z64 z = mk(0.0, 0.0);
-  launch_reduced_oe(p, op.n, op.V, op.blocks(p), op.scales(p), inv, invsc, src, t,
-                    op.nbr.as<int>(), op.osite.as<int>(), nullptr, st);
-  launch_reduced_eo(p, 0, op.n, op.V, op.blocks(p), op.scales(p), nullptr, nullptr, src, t,
+  launch_reduced_oe(p, op.n, op.V, op.blocks(p), op.scales(p), inv, invsc, in, t,
+                    op.nbr.as<int>(), op.osite.as<int>(), nullptr, st, nullptr, nullptr, adjoint);
+  launch_reduced_eo(p, 0, op.n, op.V, op.blocks(p), op.scales(p), nullptr, nullptr, in, t,
                     op.nbr.as<int>(), op.esite.as<int>(), tm, out, nullptr, nullptr, z, z, z,
-                    nullptr, st);
-  if (adjoint) launch_gamma5(p, out, out, half, op.n, st);
+                    nullptr, st, nullptr, nullptr, adjoint);
 }
 
 void op_apply_bj(Op& op, const void* in, void* out, hipStream_t st) {
@@ -960,9 +965,12 @@ struct Krylov {
       ++matvecs;
       return;
     }
-    stage(in, done);
-    if (bjinv) launch_bj_gather_store(p, op.n, rows, bjinv, bjsc, gb, out, done, st);
-    else launch_gather_store(p, op.n, rows, gb, out, done, st);
+    if (bjinv) {
+      stage(in, done);
+      launch_bj_gather_store(p, op.n, rows, bjinv, bjsc, gb, out, done, st);
+    } else {
+      apply_store(op, p, in != out && apply_one_launch(p, op.n, op.V), in, gb, out, tm, done, st);
+    }
     ++matvecs;
   }
 

@@ -190,3 +190,33 @@ def test_gram_schmidt_fp32_recycled(ortho):
         assert rc == 0 and st[0]["rel_res_true"] <= 1e-10, st
         assert oracle_relres(oop, x.cpu().numpy(), b.numpy()) <= 1e-10
     gop.close()
+
+
+# The full-lattice apply's routes, forward and adjoint, in every precision: one launch up
+# to 32 MB of blocks and two beyond (full and ragged tiles just on either side; FP64 tiles
+# of n > 40 always two), non-temporal block loads beyond 256 MB, a degenerate extent.
+# Bounds: those of the other apply comparisons with the oracle.
+@pytest.mark.parametrize("dims,ntv", [((4, 4, 4, 4), 20), ((4, 4, 4, 4), 21),
+                                      ((5, 4, 4, 3), 22), ((6, 5, 6, 6), 8), ((8, 7, 5, 6), 9),
+                                      ((9, 7, 5, 11), 13), ((1, 7, 8, 8), 16),
+                                      ((6, 5, 4, 8), 31)])
+@pytest.mark.parametrize("mu", [0.0, 0.21])
+def test_apply_routes(dims, ntv, mu):
+    from oracle import mixed
+    from oracle import operator as dop
+    from .helpers import rel
+    small = dims[0] * dims[1] * dims[2] * dims[3] * 20 * ntv * ntv * 16 < 64 << 20
+    gop, oop = make_pair(dims, ntv, 2.5, mu=mu, store=("f64", "f32", "f16s"))
+    x = rand_vec(oop.V, oop.n, 7)
+    xg, x = x.cuda(), x.numpy()
+    refa = dop.apply_adjoint(oop, x)
+    assert rel(gop.apply(xg).cpu().numpy(), dop.apply(oop, x)) <= 1e-13
+    assert rel(gop.apply(xg, adjoint=True).cpu().numpy(), refa) <= 1e-13
+    x32 = xg.to(torch.complex64)
+    for prec in ("f32", "f16s"):
+        if small:   # the oracle's rounded blocks of larger operators take minutes
+            lo = mixed.lowprec_apply(oop, prec)(x)
+            assert rel(gop.apply(x32, prec=prec).cpu().numpy(), lo) <= 2e-6, prec
+        assert rel(gop.apply(x32, prec=prec, adjoint=True).cpu().numpy(), refa) <= (
+            2e-6 if prec == "f32" else 3e-3), prec
+    gop.close()
