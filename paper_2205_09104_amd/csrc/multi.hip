@@ -278,14 +278,18 @@ __global__ __launch_bounds__(256, T <= 6 ? 2 : 1) void k_apply_multi_f64(MultiOp
 // are fewer.  The couplings' blocks go through LDS as FP16 pairs (double
 // buffered, one barrier per coupling, rows padded to an odd number of 16-byte
 // units: conflict-free fragment reads); the panels go from memory to the wave
-// that multiplies them, which holds its fragments in registers.
+// that multiplies them, which holds its fragments in registers and splits them one
+// k step at a time, between the products.
 // Measured (16^4, n = 48, 64 right-hand sides; FP32 matrix instructions and
-// planes in LDS before): FP32 6.72 -> 4.55 ms, FP16 blocks 6.86 -> 3.97 ms; 12
-// right-hand sides: 2.41 -> 1.82 and 2.38 -> 1.19 ms.  At 64, matrix cores 20%,
-// vector ALU (the splits) 39% busy; what is left is the wait for panels and
-// blocks (19 GB through the L2s, 7.7 GB once each).  At three waves per SIMD the
-// registers spill: 5.9 ms.  Three couplings in flight instead of one cost more
-// occupancy than they gain (n = 16, 32: 10% slower).
+// planes in LDS before): FP32 6.72 -> 3.95 ms, FP16 blocks 6.86 -> 3.13 ms; 12
+// right-hand sides: 2.41 -> 1.83 and 2.38 -> 1.2 ms.  At 64, matrix cores 24%,
+// vector ALU (the splits) 45% busy.  Neither bounds it: with the products or the
+// splits left out it takes as long.  What is left is the traffic of a workgroup's own
+// memories: fragment reads of the block by each of four waves (a third of the
+// reads: 0.4 ms less) and the panels' way through the L1 and the strips (19 GB
+// through the L2s, 7.7 GB once each; all loads from one site's data: 0.7 ms less).
+// Three couplings in flight instead of one cost more occupancy than they gain
+// (n = 16, 32: 10% slower).
 
 // Power-of-two scale that takes a largest magnitude m to [2^14, 2^15), and its
 // inverse; both stay normal numbers (m below 2^-112 scales to less, infinite
@@ -317,11 +321,20 @@ struct SplitShape {
   static constexpr int KG = (KS == 1 || CT == 4) ? 1 : (KS == 2 || CT == 2) ? 2 : 4;
   static constexpr int KSW = (KS + KG - 1) / KG;      // k steps per wave
   static constexpr int WPS = CT * KG, SPB = 4 / WPS;  // waves per site, sites per workgroup
+  // Panels of more than 16 columns come in 128-byte segments and turn into fragments
+  // through LDS: a fragment's own loads touch 64 cache lines each, and their look-ups
+  // bounded the kernel.  16 columns (bound by the blocks) are loaded as fragments.
+  // 16^4, n = 48, FP32, fragments / segments: 64 columns 4.6 / 3.95 ms, 32 5.6 / 5.1,
+  // 16 1.84 / 1.91.
+  static constexpr bool STRIP = CT > 1;
+  // workgroups per CU that the registers are held to (three: 168, T = 6 at 64 columns
+  // spills two; against two there: 3.95 / 4.18 ms)
+  static constexpr int WAVES = T > 6 ? 2 : STRIP ? 3 : 4;
 };
 
 template <int T, int P, int RB>
-__global__ __launch_bounds__(256, 2) void k_apply_multi_split(MultiOps ops, unsigned sites,
-                                                              int chunk) {
+__global__ __launch_bounds__(256, (SplitShape<T, RB>::WAVES)) void k_apply_multi_split(
+    MultiOps ops, unsigned sites, int chunk) {
   using Sh = SplitShape<T, RB>;
   constexpr int NP = Sh::NP, RT = Sh::RT, KS = Sh::KS, CT = Sh::CT, KG = Sh::KG, KSW = Sh::KSW;
   constexpr int WPS = Sh::WPS, SPB = Sh::SPB;
@@ -334,6 +347,7 @@ __global__ __launch_bounds__(256, 2) void k_apply_multi_split(MultiOps ops, unsi
   constexpr int UPL = (TT + EPL - 1) / EPL;       // units per lane of a block
   constexpr int MU = (UPL + WPS - 1) / WPS;       // units per thread
   __shared__ __align__(16) unsigned char lds_all[SPB * SLDS];
+  __shared__ __align__(16) unsigned char strips[Sh::STRIP ? 4 * 2048 : 16];   // a panel strip per wave
   static_assert((KG - 1) * CT * RT * 2 * 64 * 16 <= SLDS, "partial panels fit");
   const int gwave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), lane = threadIdx.x & 63;
   const int slot = gwave / WPS, wave = gwave % WPS;
@@ -366,13 +380,25 @@ __global__ __launch_bounds__(256, 2) void k_apply_multi_split(MultiOps ops, unsi
   const int lbase = lr * T * LDA + lc * T * 4, lbase_t = lc * T * LDA + lr * T * 4;
   const int rc = min(r0 + ct * 16 + l16, R - 1);  // lanes past R repeat the last column
   const auto xr = (gptr<z32>)(((gptr<const void*>)op.xin)[rc]);
-  // panel entries 16 ks + 4 lk + 2 q and the next, ks = kg + KG t; past n the last
-  // pair is read again (the blocks are zero there)
-  int joff[KSW][2];
+  // Panel loads of k step ks = kg + KG t, q = 0, 1.  As fragments: entries 16 ks + 4 lk
+  // + 2 q and the next of column l16.  As segments (STRIP): eight lanes for entries 16 ks
+  // .. 16 ks + 15 of each of columns 8 q .. 8 q + 7, and the wave's LDS strip hands them
+  // on as fragments; a column's eight units are permuted by its number so that the
+  // reads spread over the banks.  Past n the last pair is read again (the blocks are
+  // zero there).
+  constexpr bool STRIP = Sh::STRIP;
+  gptr<z32> xq[2];
+  int joff[KSW][2], spos[2], fpos[2];
 #pragma unroll
-  for (int t = 0; t < KSW; ++t)
+  for (int q = 0; q < 2; ++q) {
+    const int col = STRIP ? 8 * q + (lane >> 3) : l16, u = STRIP ? lane & 7 : 2 * lk + q;
+    xq[q] = (gptr<z32>)(((gptr<const void*>)op.xin)[min(r0 + ct * 16 + col, R - 1)]);
+    spos[q] = col * 8 + (u ^ ((col >> 1) & 7));
+    fpos[q] = l16 * 8 + ((2 * lk + q) ^ ((l16 >> 1) & 7));
 #pragma unroll
-    for (int q = 0; q < 2; ++q) joff[t][q] = min(16 * (kg + KG * t) + 4 * lk + 2 * q, n - 2);
+    for (int t = 0; t < KSW; ++t) joff[t][q] = min(16 * (kg + KG * t) + 2 * u, n - 2);
+  }
+  f4* const strip = reinterpret_cast<f4*>(strips) + (STRIP ? gwave * 128 : 0);
 
   u4 araw[MU];
   f4 braw[KSW][2];
@@ -385,11 +411,11 @@ __global__ __launch_bounds__(256, 2) void k_apply_multi_split(MultiOps ops, unsi
     }
   };
   auto load_panel = [&](int src) {
-    const auto x = xr + size_t(src) * n;
+    const size_t x = size_t(src) * n;
 #pragma unroll
     for (int t = 0; t < KSW; ++t)
 #pragma unroll
-      for (int q = 0; q < 2; ++q) braw[t][q] = *(gptr<f4>)(x + joff[t][q]);
+      for (int q = 0; q < 2; ++q) braw[t][q] = *(gptr<f4>)(xq[q] + x + joff[t][q]);
   };
   auto store_block = [&](unsigned char* buf, float scale, bool trans) {
     float up = 1.f, down = 1.f;
@@ -453,89 +479,102 @@ __global__ __launch_bounds__(256, 2) void k_apply_multi_split(MultiOps ops, unsi
   for (int c = 0; c < 9; ++c) {
     unsigned char* buf = lds + (c & 1) * (PIECES * PLANE);
     __syncthreads();   // buf is complete, and the other buffer's products are done
-    // this coupling's panel -> scaled FP16 fragments
+    // this coupling's panel -> scaled FP16 fragments (LDS keeps the order of a wave's
+    // accesses to its strip)
+    f4 fr[KSW][2];
+#pragma unroll
+    for (int t = 0; t < KSW; ++t) {
+      if constexpr (STRIP) {
+        strip[spos[0]] = braw[t][0];
+        strip[spos[1]] = braw[t][1];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        fr[t][0] = strip[fpos[0]];
+        fr[t][1] = strip[fpos[1]];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      } else {
+        fr[t][0] = braw[t][0];
+        fr[t][1] = braw[t][1];
+      }
+    }
     float mx = 0.f;
 #pragma unroll
     for (int t = 0; t < KSW; ++t)
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
-        mx = fmaxf(fmaxf(mx, fabsf(braw[t][q].x)), fabsf(braw[t][q].y));
-        mx = fmaxf(fmaxf(mx, fabsf(braw[t][q].z)), fabsf(braw[t][q].w));
+        mx = fmaxf(fmaxf(mx, fabsf(fr[t][q].x)), fabsf(fr[t][q].y));
+        mx = fmaxf(fmaxf(mx, fabsf(fr[t][q].z)), fabsf(fr[t][q].w));
       }
     mx = fmaxf(mx, shfl_xor(mx, 16));
     mx = fmaxf(mx, shfl_xor(mx, 32));
     float up, down;
     pow2_scale(mx, up, down);
-    u4 bh[KSW], bl[KSW];     // (pi, pr) pairs: the Im operand
-    u4 bhr[KSW], blr[KSW];   // (pr, -pi): swapped, the high half negated
-#pragma unroll
-    for (int t = 0; t < KSW; ++t)
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        float u0 = up, u1 = up;
-        if (g5in) {
-          u0 = joff[t][q] < half ? up : -up;
-          u1 = joff[t][q] + 1 < half ? up : -up;
-        }
-        const f4 z = braw[t][q];
-        uint32_t h[2], l[2];
-        split_pair(z.y * u0, z.x * u0, h[0], l[0]);
-        split_pair(z.w * u1, z.z * u1, h[1], l[1]);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          bh[t][2 * q + i] = h[i];
-          bl[t][2 * q + i] = l[i];
-          bhr[t][2 * q + i] = __builtin_amdgcn_alignbit(h[i], h[i], 16) ^ 0x80000000u;
-          blr[t][2 * q + i] = __builtin_amdgcn_alignbit(l[i], l[i], 16) ^ 0x80000000u;
-        }
-      }
     float fblk = scale_of(c);
     if (P == P32) {
       float u;
       pow2_scale(fblk, u, fblk);
     }
+    if (c + 1 < 9) load_panel(source(c + 1));
     // the next panel and block are in flight, and the next block's pieces are
     // written, while this coupling multiplies
     if (c + 1 < 9) {
-      load_panel(source(c + 1));
       unsigned char* nb = lds + ((c + 1) & 1) * (PIECES * PLANE);
       if (coupling(c + 1) < 5) store_block(nb, scale_of(c + 1), false);
       else store_block(nb, scale_of(c + 1), true);
       if (c + 2 < 9) load_block(block_of(c + 2));
     }
-    if (KS % KG == 0 || kg < KS) {   // a wave with no k step of its own only stages
+    f4 are[RT], aim[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) are[rt] = aim[rt] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < KSW; ++t) {
+      if (KS % KG != 0 && kg + KG * t >= KS) continue;
+      u4 bh, bl, bhr, blr;   // (pi, pr) pairs: the Im operand; (pr, -pi): swapped, high half negated
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        float u0 = up, u1 = up;
+        if (g5in) {
+          const int j = 16 * (kg + KG * t) + 4 * lk + 2 * q;
+          u0 = j < half ? up : -up;
+          u1 = j + 1 < half ? up : -up;
+        }
+        const f4 z = fr[t][q];
+        uint32_t h[2], l[2];
+        split_pair(z.y * u0, z.x * u0, h[0], l[0]);
+        split_pair(z.w * u1, z.z * u1, h[1], l[1]);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          bh[2 * q + i] = h[i];
+          bl[2 * q + i] = l[i];
+          bhr[2 * q + i] = __builtin_amdgcn_alignbit(h[i], h[i], 16) ^ 0x80000000u;
+          blr[2 * q + i] = __builtin_amdgcn_alignbit(l[i], l[i], 16) ^ 0x80000000u;
+        }
+      }
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
         const unsigned char* row = buf + (rt * 16 + l16) * LDA + lk * 16 + kg * 64;
-        f4 are = f4{0.f, 0.f, 0.f, 0.f}, aim = are;
-        h8 ah[KSW];
+        const h8 ah = *reinterpret_cast<const h8*>(row + t * KG * 64);
         // small products first
-#pragma unroll
-        for (int t = 0; t < KSW; ++t) {
-          if (KS % KG != 0 && KSW > 1 && kg + KG * t >= KS) continue;
-          ah[t] = *reinterpret_cast<const h8*>(row + t * KG * 64);
-          are = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[t], __builtin_bit_cast(h8, blr[t]), are, 0, 0, 0);
-          aim = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[t], __builtin_bit_cast(h8, bl[t]), aim, 0, 0, 0);
-          if constexpr (PIECES == 2) {
-            const h8 al = *reinterpret_cast<const h8*>(row + PLANE + t * KG * 64);
-            are = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, __builtin_bit_cast(h8, bhr[t]), are, 0, 0, 0);
-            aim = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, __builtin_bit_cast(h8, bh[t]), aim, 0, 0, 0);
-          }
+        are[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, __builtin_bit_cast(h8, blr), are[rt], 0, 0, 0);
+        aim[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, __builtin_bit_cast(h8, bl), aim[rt], 0, 0, 0);
+        if constexpr (PIECES == 2) {
+          const h8 al = *reinterpret_cast<const h8*>(row + PLANE + t * KG * 64);
+          are[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, __builtin_bit_cast(h8, bhr), are[rt], 0, 0, 0);
+          aim[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, __builtin_bit_cast(h8, bh), aim[rt], 0, 0, 0);
         }
-#pragma unroll
-        for (int t = 0; t < KSW; ++t) {
-          if (KS % KG != 0 && KSW > 1 && kg + KG * t >= KS) continue;
-          are = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[t], __builtin_bit_cast(h8, bhr[t]), are, 0, 0, 0);
-          aim = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[t], __builtin_bit_cast(h8, bh[t]), aim, 0, 0, 0);
-        }
-        // scales undone in FP32: the column's own, then the block's
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          tre[rt][q] = fmaf(are[q] * down, fblk, tre[rt][q]);
-          tim[rt][q] = fmaf(aim[q] * down, fblk, tim[rt][q]);
-        }
+        are[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, __builtin_bit_cast(h8, bhr), are[rt], 0, 0, 0);
+        aim[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, __builtin_bit_cast(h8, bh), aim[rt], 0, 0, 0);
       }
     }
+    // scales undone in FP32: the column's own, then the block's
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        tre[rt][q] = fmaf(are[rt][q] * down, fblk, tre[rt][q]);
+        tim[rt][q] = fmaf(aim[rt][q] * down, fblk, tim[rt][q]);
+      }
   }
   // the k shares of a column tile added in wave order
   if (KG > 1) {
