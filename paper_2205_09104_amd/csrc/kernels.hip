@@ -1278,30 +1278,39 @@ __global__ void k_oddeven_split(int n, int H, const int* __restrict__ esite,
 }
 
 // ------------------------------------------------------------------ gradient
-__global__ void k_grad_hops(const z64* __restrict__ lam, const z64* __restrict__ x,
-                            z64* __restrict__ grad, const int* __restrict__ nbr, int V, int n,
-                            int tied) {
+// d S / d B[x, dir]: the n x n outer products of a site and its neighbour, bound by the
+// writes.  A thread keeps column j for every 256 / n rows, so its neighbour entries are
+// read once and nothing is divided in the loop.  8^4, n = 32, tied (268 MB): 50.6 us
+// with a division per entry, 48.3 now, 5.6 TB/s (non-temporal stores: 51).
+__global__ __launch_bounds__(256) void k_grad_hops(const z64* __restrict__ lam,
+                                                   const z64* __restrict__ x,
+                                                   z64* __restrict__ grad,
+                                                   const int* __restrict__ nbr, int V, int n,
+                                                   int tied) {
+  typedef double d2 __attribute__((ext_vector_type(2)));
   const int site = blockIdx.x;
   const int dir = blockIdx.y;  // 0..7 untied, 0..3 tied
+  const int rows = 256 / n;    // n <= 64
+  const int i0 = int(threadIdx.x) / n, j = int(threadIdx.x) - i0 * n;
+  if (i0 >= rows) return;
   const int y = nbr[dir * V + site];
-  const size_t nn = size_t(n) * n;
-  z64* out = grad + (size_t(site) * (tied ? 4 : 8) + dir) * nn;
-  for (size_t t = threadIdx.x; t < nn; t += blockDim.x) {
-    const int i = int(t / n), j = int(t % n);
+  d2* out = reinterpret_cast<d2*>(grad) + (size_t(site) * (tied ? 4 : 8) + dir) * (size_t(n) * n) + j;
+  const z64 xv = x[size_t(y) * n + j];
+  const z64 ly = tied ? lam[size_t(y) * n + j] : mk(0.0, 0.0);
+  const double gj = gam(j, n);
+  for (int i = i0; i < n; i += rows) {
     const z64 l = lam[size_t(site) * n + i];
-    const z64 xv = x[size_t(y) * n + j];
     // -lambda_x,i * conj(x_y,j)
     double gr = -(l.re * xv.re + l.im * xv.im);
     double gi = -(l.im * xv.re - l.re * xv.im);
     if (tied) {
       // - g5_i x_x,i conj(lambda_y,j) g5_j
       const z64 xx = x[size_t(site) * n + i];
-      const z64 ly = lam[size_t(y) * n + j];
-      const double s = gam(i, n) * gam(j, n);
+      const double s = gam(i, n) * gj;
       gr -= s * (xx.re * ly.re + xx.im * ly.im);
       gi -= s * (xx.im * ly.re - xx.re * ly.im);
     }
-    out[t] = mk(gr, gi);
+    out[size_t(i) * n] = d2{gr, gi};
   }
 }
 
