@@ -305,13 +305,13 @@ __device__ inline void tile_products(const TileRegs<T, P>& R, const cx<A> (&pc)[
 // One stored block of one site, processed by one wave.  Full lattice (the
 // default): the self block writes slot 4 of gbuf[x]; a hop block B[x,mu]
 // writes B psi_{x+mu} into slot 5+mu of gbuf[x] and Gamma5 B^H Gamma5 psi_x
-// into slot mu of gbuf[x+mu].  g5: Gamma5 before and after (the adjoint through
+// into slot mu of gbuf[x+mu].  G5: Gamma5 before and after (the adjoint through
 // Gamma5 D(-mu) Gamma5), as signs of the products' inputs and outputs.
-template <int T, int P, bool FULL, bool HOP>
+template <int T, int P, bool FULL, bool HOP, bool G5>
 __device__ __forceinline__ void apply_one_block(
     const uint4* __restrict__ bp, const float* __restrict__ scales,
     const cx<typename VecOf<P>::R>* __restrict__ psi, cx<typename VecOf<P>::R>* __restrict__ gbuf,
-    int item, int site, int slot, int src, int n, double tm, int g5, int stream) {
+    int item, int site, int slot, int src, int n, double tm, int stream) {
   using A = typename Tile<T, P>::A;
   using VR = typename VecOf<P>::R;
   constexpr bool DOG = HOP;
@@ -328,7 +328,7 @@ __device__ __forceinline__ void apply_one_block(
     pc[q] = mk(A(0), A(0));
     if (FULL || col < n) {
       const cx<VR> z = psi[size_t(HOP ? src : site) * n + col];
-      pc[q] = (g5 && col >= (n >> 1)) ? mk(A(-z.re), A(-z.im)) : mk(A(z.re), A(z.im));
+      pc[q] = (G5 && col >= (n >> 1)) ? mk(A(-z.re), A(-z.im)) : mk(A(z.re), A(z.im));
     }
     npc_im[q] = -pc[q].im;
     pr[q] = mk(A(0), A(0));
@@ -336,7 +336,7 @@ __device__ __forceinline__ void apply_one_block(
       const int row = lr * T + q;
       if (FULL || row < n) {
         const cx<VR> z = psi[size_t(site) * n + row];
-        pr[q] = (g5 || row < (n >> 1)) ? mk(A(z.re), A(z.im)) : mk(A(-z.re), A(-z.im));
+        pr[q] = (G5 || row < (n >> 1)) ? mk(A(z.re), A(z.im)) : mk(A(-z.re), A(-z.im));
       }
     }
     npr_re[q] = -pr[q].re;
@@ -363,7 +363,7 @@ __device__ __forceinline__ void apply_one_block(
       if (FULL || row < n) {
         const bool low = row >= (n >> 1);
         cx<A> v = f[q];
-        if (g5 && low) v = mk(-v.re, -v.im);
+        if (G5 && low) v = mk(-v.re, -v.im);
         if (!HOP && tm != 0.0) {  // i * tm * Gamma5 psi_x in the accumulation precision
           const A t = A(low ? -tm : tm);
           const cx<VR> z = psi[size_t(site) * n + row];
@@ -386,7 +386,7 @@ __device__ __forceinline__ void apply_one_block(
       for (int q = 0; q < T; ++q) {
         const int col = lc * T + q;
         if (FULL || col < n) {
-          const A gg = (g5 || col < (n >> 1)) ? A(1) : A(-1);
+          const A gg = (G5 || col < (n >> 1)) ? A(1) : A(-1);
           dst[col] = mk(VR(gg * g[q].re), VR(gg * g[q].im));
         }
       }
@@ -401,11 +401,11 @@ __device__ __forceinline__ void apply_one_block(
 // of different sites overlap their loads with each other's arithmetic.  HBM bound
 // with blocks beyond the last-level cache: 16^4, n = 48, FP16: 572 us, 5.5 TB/s of
 // block and vector bytes (607 with cached loads); 8^4, n = 48, FP64: 133 us (149).
-template <int T, int P, bool FULL>
+template <int T, int P, bool FULL, bool G5>
 __global__ __launch_bounds__(64) void k_apply_blocks(
     const void* __restrict__ blocks, const float* __restrict__ scales,
     const cx<typename VecOf<P>::R>* __restrict__ psi, cx<typename VecOf<P>::R>* __restrict__ gbuf,
-    const int* __restrict__ nbr, int V, int n, int chunk, double tm, int g5,
+    const int* __restrict__ nbr, int V, int n, int chunk, double tm,
     int stream, const int* __restrict__ done) {
   if (done && *done) return;
   // XCD-aware order: workgroup b runs on XCD b % 8; each XCD gets a
@@ -418,10 +418,10 @@ __global__ __launch_bounds__(64) void k_apply_blocks(
   const size_t blk_units = size_t(Tile<T, P>::UNITS) * 64;
   const uint4* bp = static_cast<const uint4*>(blocks) + size_t(item) * blk_units;
   if (slot == 0) {
-    apply_one_block<T, P, FULL, false>(bp, scales, psi, gbuf, item, site, 0, site, n, tm, g5, stream);
+    apply_one_block<T, P, FULL, false, G5>(bp, scales, psi, gbuf, item, site, 0, site, n, tm, stream);
   } else {
     const int src = nbr[(slot - 1) * V + site];
-    apply_one_block<T, P, FULL, true>(bp, scales, psi, gbuf, item, site, slot, src, n, tm, g5, stream);
+    apply_one_block<T, P, FULL, true, G5>(bp, scales, psi, gbuf, item, site, slot, src, n, tm, stream);
   }
 }
 
@@ -576,13 +576,13 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_apply_site(
 // Gamma5 B[x-mu,mu]^H Gamma5 x_e(x-mu), then wave 8 applies the inverse of
 // x's self block to the sum of the eight products.
 // Rows are ordered XCD-aware as in k_apply_blocks (contiguous rows per XCD).
-template <int T, int P, bool FULL>
+template <int T, int P, bool FULL, bool G5>
 __global__ __launch_bounds__(64 * kRedWaves) void k_reduced_oe(
     const void* __restrict__ blocks, const float* __restrict__ scales,
     const void* __restrict__ inv, const float* __restrict__ invsc,
     const cx<typename VecOf<P>::R>* __restrict__ x_e, cx<typename VecOf<P>::R>* __restrict__ t_o,
     const int* __restrict__ nbr, const int* __restrict__ osite, int V, int n, int chunk,
-    int g5, const int* __restrict__ done) {
+    const int* __restrict__ done) {
   using A = typename Tile<T, P>::A;
   using VR = typename VecOf<P>::R;
   __shared__ cx<VR> part[8][64];
@@ -598,14 +598,14 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduced_oe(
     R.load(block_ptr<T, P>(blocks, size_t(item)), lane);
     const A s = (P == P16S) ? A(scales[item]) : A(1);
     const int src = nbr[w * V + x];
-    wave_product<T, P, FULL, 1>(R, s, x_e + size_t(src >> 1) * n, part[w], n, 0.0, lane, g5 & 1);
+    wave_product<T, P, FULL, 1>(R, s, x_e + size_t(src >> 1) * n, part[w], n, 0.0, lane, G5 ? 1 : 0);
   } else if (w < 8) {
     const int mu = w - 4;
     const int y = nbr[(4 + mu) * V + x];
     const int item = 5 * y + 1 + mu;
     R.load(block_ptr<T, P>(blocks, size_t(item)), lane);
     const A s = (P == P16S) ? A(scales[item]) : A(1);
-    wave_product<T, P, FULL, 2>(R, s, x_e + size_t(y >> 1) * n, part[w], n, 0.0, lane, g5 & 1);
+    wave_product<T, P, FULL, 2>(R, s, x_e + size_t(y >> 1) * n, part[w], n, 0.0, lane, G5 ? 1 : 0);
   }
   __syncthreads();
   if (w != 8) return;
@@ -696,14 +696,14 @@ __device__ __forceinline__ void reduced_epilogue(size_t i, cx<VR> t, cx<VR>* out
 // (einv, same tiled layout, indexed by site) before the barrier, in place of
 // the self block, and applies it to the sum of the eight hop products.
 // Epilogue on row r: reduced_epilogue<EPI> (EPI 3 only without BJ).
-template <int T, int P, bool FULL, int EPI, bool BJ>
+template <int T, int P, bool FULL, int EPI, bool BJ, bool G5>
 __global__ __launch_bounds__(64 * kRedWaves) void k_reduced_eo(
     const void* __restrict__ blocks, const float* __restrict__ scales,
     const void* __restrict__ einv, const float* __restrict__ einvsc,
     const cx<typename VecOf<P>::R>* x_e, const cx<typename VecOf<P>::R>* __restrict__ t_o,
     const int* __restrict__ nbr, const int* __restrict__ esite, int V, int n, int chunk, double tm,
     cx<typename VecOf<P>::R>* out, const cx<typename VecOf<P>::R>* e, cx<typename VecOf<P>::R>* y,
-    z64 c0, z64 ca, z64 cb, int g5, const int* __restrict__ done) {
+    z64 c0, z64 ca, z64 cb, const int* __restrict__ done) {
   using A = typename Tile<T, P>::A;
   using VR = typename VecOf<P>::R;
   __shared__ cx<VR> part[kRedWaves][64];
@@ -732,7 +732,7 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduced_eo(
       const int item = 5 * x;
       R.load(block_ptr<T, P>(blocks, size_t(item)), lane);
       const A s = (P == P16S) ? A(scales[item]) : A(1);
-      wave_product<T, P, FULL, 0>(R, s, x_e + size_t(r) * n, part[0], n, tm, lane, g5 & 1);
+      wave_product<T, P, FULL, 0>(R, s, x_e + size_t(r) * n, part[0], n, tm, lane, G5 ? 1 : 0);
     } else {
       for (int i = lane; i < n; i += 64) part[0][i] = mk(VR(0), VR(0));
     }
@@ -794,11 +794,11 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduced_eo(
     cx<VR> t = mk(VR(mine.re), VR(mine.im));
     if (x_e) {
       const cx<VR> xv = x_e[i];
-      const VR sx = VR((g5 && row >= (n >> 1)) ? -1 : 1);
+      const VR sx = VR((G5 && row >= (n >> 1)) ? -1 : 1);
       t.re += sx * xv.re;
       t.im += sx * xv.im;
     }
-    if (g5 && row >= (n >> 1)) t = mk(-t.re, -t.im);
+    if (G5 && row >= (n >> 1)) t = mk(-t.re, -t.im);
     reduced_epilogue<EPI>(i, t, out, e, y, c0, ca, cb);
   } else {
     for (int c = lane; c < n; c += 64) {
@@ -808,7 +808,7 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduced_eo(
         t.re += part[k][c].re;
         t.im += part[k][c].im;
       }
-      if (g5 && c >= (n >> 1)) t = mk(-t.re, -t.im);
+      if (G5 && c >= (n >> 1)) t = mk(-t.re, -t.im);
       reduced_epilogue<EPI>(size_t(r) * n + c, t, out, e, y, c0, ca, cb);
     }
   }
@@ -845,13 +845,13 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduced_eo(
 template <int T, int P>
 constexpr int scatter_min_waves() { return (P == P16S && T <= 6) ? 7 : 1; }
 
-template <int T, int P, bool FULL>
+template <int T, int P, bool FULL, bool G5>
 __global__ __launch_bounds__(512, (scatter_min_waves<T, P>())) void k_reduced_scatter(
     const void* __restrict__ blocks, const float* __restrict__ scales,
     const void* __restrict__ inv, const float* __restrict__ invsc,
     const cx<typename VecOf<P>::R>* __restrict__ x_e, cx<typename VecOf<P>::R>* __restrict__ hp,
     const int* __restrict__ nbr, const int* __restrict__ osite, int V, int n, int chunk,
-    int g5, const int* __restrict__ done) {
+    const int* __restrict__ done) {
   using A = typename Tile<T, P>::A;
   using VR = typename VecOf<P>::R;
   constexpr int UNITS = Tile<T, P>::UNITS;
@@ -881,7 +881,7 @@ __global__ __launch_bounds__(512, (scatter_min_waves<T, P>())) void k_reduced_sc
     R.load_stream(block_ptr<T, P>(blocks, size_t(item)), lane);
     if (P == P16S) s = A(scales[item]);
     const int src = nbr[w * V + x];
-    wave_product<T, P, FULL, 1>(R, s, x_e + size_t(src >> 1) * n, part[w], n, 0.0, lane, g5 & 1);
+    wave_product<T, P, FULL, 1>(R, s, x_e + size_t(src >> 1) * n, part[w], n, 0.0, lane, G5 ? 1 : 0);
     dst = (size_t(src >> 1) * 8 + 4 + w) * n;        // backward hop mu = w of even x + mu
   } else {
     const int mu = w - 4;
@@ -889,7 +889,7 @@ __global__ __launch_bounds__(512, (scatter_min_waves<T, P>())) void k_reduced_sc
     const int item = 5 * y + 1 + mu;
     R.load_stream(block_ptr<T, P>(blocks, size_t(item)), lane);
     if (P == P16S) s = A(scales[item]);
-    wave_product<T, P, FULL, 2>(R, s, x_e + size_t(y >> 1) * n, part[w], n, 0.0, lane, g5 & 1);
+    wave_product<T, P, FULL, 2>(R, s, x_e + size_t(y >> 1) * n, part[w], n, 0.0, lane, G5 ? 1 : 0);
     dst = (size_t(y >> 1) * 8 + mu) * n;             // forward hop mu of even x - mu
   }
   __syncthreads();
@@ -957,14 +957,14 @@ __global__ __launch_bounds__(512, (scatter_min_waves<T, P>())) void k_reduced_sc
 // are the hop terms k_reduced_eo sums from its own products; the row is then
 // finished as there: BJ x_e + A_e^{-1} (sum), else A_e x_e (+ i tm Gamma5 x_e)
 // with the terms added one by one, and the epilogue.
-template <int T, int P, bool FULL, int EPI, bool BJ>
+template <int T, int P, bool FULL, int EPI, bool BJ, bool G5>
 __global__ __launch_bounds__(64) void k_reduced_gather(
     const void* __restrict__ blocks, const float* __restrict__ scales,
     const void* __restrict__ einv, const float* __restrict__ einvsc,
     const cx<typename VecOf<P>::R>* x_e, const cx<typename VecOf<P>::R>* __restrict__ hp,
     const int* __restrict__ esite, int V, int n, int chunk, double tm,
     cx<typename VecOf<P>::R>* out, const cx<typename VecOf<P>::R>* e, cx<typename VecOf<P>::R>* y,
-    z64 c0, z64 ca, z64 cb, int g5, const int* __restrict__ done) {
+    z64 c0, z64 ca, z64 cb, const int* __restrict__ done) {
   using A = typename Tile<T, P>::A;
   using VR = typename VecOf<P>::R;
   __shared__ cx<VR> self_part[64];
@@ -1019,18 +1019,18 @@ __global__ __launch_bounds__(64) void k_reduced_gather(
     cx<VR> o = mk(VR(mine.re), VR(mine.im));
     if (x_e) {
       const cx<VR> xv = x_e[i];
-      const VR sx = VR((g5 && row >= (n >> 1)) ? -1 : 1);
+      const VR sx = VR((G5 && row >= (n >> 1)) ? -1 : 1);
       o.re += sx * xv.re;
       o.im += sx * xv.im;
     }
-    if (g5 && row >= (n >> 1)) o = mk(-o.re, -o.im);
+    if (G5 && row >= (n >> 1)) o = mk(-o.re, -o.im);
     reduced_epilogue<EPI>(i, o, out, e, y, c0, ca, cb);
   } else {
     if (x_e) {
       const int item = 5 * x;
       R.load_stream(block_ptr<T, P>(blocks, size_t(item)), lane);
       const A s = (P == P16S) ? A(scales[item]) : A(1);
-      wave_product<T, P, FULL, 0>(R, s, x_e + size_t(r) * n, self_part, n, tm, lane, g5 & 1);
+      wave_product<T, P, FULL, 0>(R, s, x_e + size_t(r) * n, self_part, n, tm, lane, G5 ? 1 : 0);
     } else {
       self_part[lane] = mk(VR(0), VR(0));
     }
@@ -1042,7 +1042,7 @@ __global__ __launch_bounds__(64) void k_reduced_gather(
       o.re += -h[k].re;
       o.im += -h[k].im;
     }
-    if (g5 && lane >= (n >> 1)) o = mk(-o.re, -o.im);
+    if (G5 && lane >= (n >> 1)) o = mk(-o.re, -o.im);
     reduced_epilogue<EPI>(size_t(r) * n + lane, o, out, e, y, c0, ca, cb);
   }
 }
@@ -1348,15 +1348,14 @@ static void apply_T(int n, int V, const void* blocks, const float* scales, const
   const bool full = (n % 8) == 0;
   switch (tile_T(n)) {
   // with events: the dispatch itself records its start and end (no marker packets)
-#define DC_CASE(TV)                                                                           \
-  case TV:                                                                                    \
-    if (full)                                                                                 \
-      hipExtLaunchKernelGGL((k_apply_blocks<TV, P, true>), grid, block, 0, st, ev0, ev1, 0,   \
-                            blocks, scales, pin, pg, nbr, V, n, chunk, tm, g5, stream, done);    \
-    else                                                                                      \
-      hipExtLaunchKernelGGL((k_apply_blocks<TV, P, false>), grid, block, 0, st, ev0, ev1, 0,  \
-                            blocks, scales, pin, pg, nbr, V, n, chunk, tm, g5, stream, done);    \
-    break;
+#define DC_CASE(TV)                                                                            \
+  case TV: {                                                                                   \
+    const auto k = full ? (g5 ? k_apply_blocks<TV, P, true, true> : k_apply_blocks<TV, P, true, false>)\
+                        : (g5 ? k_apply_blocks<TV, P, false, true> : k_apply_blocks<TV, P, false, false>);\
+    hipExtLaunchKernelGGL(k, grid, block, 0, st, ev0, ev1, 0, blocks, scales, pin, pg, nbr, V, \
+                          n, chunk, tm, stream, done);                                         \
+    break;                                                                                     \
+  }
     DC_CASE(1) DC_CASE(2) DC_CASE(3) DC_CASE(4) DC_CASE(5) DC_CASE(6) DC_CASE(7) DC_CASE(8)
 #undef DC_CASE
     default:
@@ -1499,15 +1498,14 @@ static void reduced_oe_T(int n, int V, const void* blocks, const float* scales, 
   auto* to = static_cast<cx<VR>*>(t_o);
   const bool full = (n % 8) == 0;
   switch (tile_T(n)) {
-#define DC_CASE(TV)                                                                           \
-  case TV:                                                                                    \
-    if (full)                                                                                 \
-      hipExtLaunchKernelGGL((k_reduced_oe<TV, P, true>), grid, block, 0, st, ev0, ev1, 0,     \
-                            blocks, scales, inv, invsc, xe, to, nbr, osite, V, n, chunk, g5, done); \
-    else                                                                                      \
-      hipExtLaunchKernelGGL((k_reduced_oe<TV, P, false>), grid, block, 0, st, ev0, ev1, 0,    \
-                            blocks, scales, inv, invsc, xe, to, nbr, osite, V, n, chunk, g5, done); \
-    break;
+#define DC_CASE(TV)                                                                            \
+  case TV: {                                                                                   \
+    const auto k = full ? (g5 ? k_reduced_oe<TV, P, true, true> : k_reduced_oe<TV, P, true, false>)\
+                        : (g5 ? k_reduced_oe<TV, P, false, true> : k_reduced_oe<TV, P, false, false>);\
+    hipExtLaunchKernelGGL(k, grid, block, 0, st, ev0, ev1, 0, blocks, scales, inv, invsc, xe,  \
+                          to, nbr, osite, V, n, chunk, done);                                  \
+    break;                                                                                     \
+  }
     DC_CASE(1) DC_CASE(2) DC_CASE(3) DC_CASE(4) DC_CASE(5) DC_CASE(6) DC_CASE(7) DC_CASE(8)
 #undef DC_CASE
     default:
@@ -1542,18 +1540,19 @@ static void reduced_eo_T(int n, int V, const void* blocks, const float* scales, 
   const auto* ee = static_cast<const cx<VR>*>(e);
   auto* yy = static_cast<cx<VR>*>(y);
   const bool full = (n % 8) == 0;
+  constexpr bool E0 = EPI == 0;   // Gamma5 comes with the plain store only
   switch (tile_T(n)) {
-#define DC_CASE(TV)                                                                              \
-  case TV:                                                                                       \
-    if (full)                                                                                    \
-      hipExtLaunchKernelGGL((k_reduced_eo<TV, P, true, EPI, BJ>), grid, block, 0, st, ev0, ev1,  \
-                            0, blocks, scales, einv, einvsc, xe, to, nbr, esite, V, n, chunk, tm, \
-                            o, ee, yy, c0, ca, cb, g5, done);                                        \
-    else                                                                                         \
-      hipExtLaunchKernelGGL((k_reduced_eo<TV, P, false, EPI, BJ>), grid, block, 0, st, ev0, ev1, \
-                            0, blocks, scales, einv, einvsc, xe, to, nbr, esite, V, n, chunk, tm, \
-                            o, ee, yy, c0, ca, cb, g5, done);                                        \
-    break;
+#define DC_CASE(TV)                                                                       \
+  case TV: {                                                                              \
+    const auto k = full ? (E0 && g5 ? k_reduced_eo<TV, P, true, EPI, BJ, E0>              \
+                                    : k_reduced_eo<TV, P, true, EPI, BJ, false>)          \
+                        : (E0 && g5 ? k_reduced_eo<TV, P, false, EPI, BJ, E0>             \
+                                    : k_reduced_eo<TV, P, false, EPI, BJ, false>);        \
+    hipExtLaunchKernelGGL(k, grid, block, 0, st, ev0, ev1, 0, blocks, scales, einv,       \
+                          einvsc, xe, to, nbr, esite, V, n, chunk, tm, o,                 \
+                          ee, yy, c0, ca, cb, done);                                      \
+    break;                                                                                \
+  }
     DC_CASE(1) DC_CASE(2) DC_CASE(3) DC_CASE(4) DC_CASE(5) DC_CASE(6) DC_CASE(7) DC_CASE(8)
 #undef DC_CASE
     default:
@@ -1592,6 +1591,7 @@ void launch_reduced_eo(Prec p, int epi, int n, int V, const void* blocks, const 
                        void* y, z64 c0, z64 ca, z64 cb, const int* done, hipStream_t st,
                        hipEvent_t ev0, hipEvent_t ev1, int g5) {
   if (epi < 0 || epi > 3) throw InvalidArg("reduced epilogue must be 0..3");
+  if (g5 && epi != 0) throw InvalidArg("Gamma5 comes with the plain store only");
   if (einv && epi == 3) throw InvalidArg("the residual epilogue takes the unpreconditioned operator");
   if (einv && p == P16S && !einvsc) throw InvalidArg("FP16 inverses need their scales");
   if (V < 2 || V % 2) throw InvalidArg("the reduced operator needs an even number of sites");
@@ -1651,18 +1651,15 @@ static void reduced_scatter_T(int n, int V, const void* blocks, const float* sca
   auto* h = static_cast<cx<VR>*>(hp);
   const bool full = (n % 8) == 0;
   switch (tile_T(n)) {
-#define DC_CASE(TV)                                                                            \
-  case TV:                                                                                     \
-    if constexpr (single_read_tile<P>(TV)) {                                                   \
-      if (full)                                                                                \
-        hipExtLaunchKernelGGL((k_reduced_scatter<TV, P, true>), grid, block, 0, st, ev0, ev1,  \
-                              0, blocks, scales, inv, invsc, xe, h, nbr, osite, V, n, chunk,   \
-                              g5, done);                                                           \
-      else                                                                                     \
-        hipExtLaunchKernelGGL((k_reduced_scatter<TV, P, false>), grid, block, 0, st, ev0, ev1, \
-                              0, blocks, scales, inv, invsc, xe, h, nbr, osite, V, n, chunk,   \
-                              g5, done);                                                           \
-    }                                                                                          \
+#define DC_CASE(TV)                                                                                    \
+  case TV:                                                                                             \
+    if constexpr (single_read_tile<P>(TV)) {                                                           \
+      const auto k =                                                                                   \
+          full ? (g5 ? k_reduced_scatter<TV, P, true, true> : k_reduced_scatter<TV, P, true, false>)   \
+               : (g5 ? k_reduced_scatter<TV, P, false, true> : k_reduced_scatter<TV, P, false, false>);\
+      hipExtLaunchKernelGGL(k, grid, block, 0, st, ev0, ev1, 0, blocks, scales, inv, invsc, xe,        \
+                            h, nbr, osite, V, n, chunk, done);                                         \
+    }                                                                                                  \
     break;
     DC_CASE(1) DC_CASE(2) DC_CASE(3) DC_CASE(4) DC_CASE(5) DC_CASE(6) DC_CASE(7) DC_CASE(8)
 #undef DC_CASE
@@ -1702,19 +1699,19 @@ static void reduced_gather_T(int n, int V, const void* blocks, const float* scal
   const auto* ee = static_cast<const cx<VR>*>(e);
   auto* yy = static_cast<cx<VR>*>(y);
   const bool full = (n % 8) == 0;
+  constexpr bool E0 = EPI == 0;   // Gamma5 comes with the plain store only
   switch (tile_T(n)) {
-#define DC_CASE(TV)                                                                             \
-  case TV:                                                                                      \
-    if constexpr (single_read_tile<P>(TV)) {                                                    \
-      if (full)                                                                                 \
-        hipExtLaunchKernelGGL((k_reduced_gather<TV, P, true, EPI, BJ>), grid, block, 0, st,     \
-                              ev0, ev1, 0, blocks, scales, einv, einvsc, xe, h, esite, V, n,    \
-                              chunk, tm, o, ee, yy, c0, ca, cb, g5, done);                          \
-      else                                                                                      \
-        hipExtLaunchKernelGGL((k_reduced_gather<TV, P, false, EPI, BJ>), grid, block, 0, st,    \
-                              ev0, ev1, 0, blocks, scales, einv, einvsc, xe, h, esite, V, n,    \
-                              chunk, tm, o, ee, yy, c0, ca, cb, g5, done);                          \
-    }                                                                                           \
+#define DC_CASE(TV)                                                                       \
+  case TV:                                                                                \
+    if constexpr (single_read_tile<P>(TV)) {                                              \
+      const auto k = full ? (E0 && g5 ? k_reduced_gather<TV, P, true, EPI, BJ, E0>        \
+                                      : k_reduced_gather<TV, P, true, EPI, BJ, false>)    \
+                          : (E0 && g5 ? k_reduced_gather<TV, P, false, EPI, BJ, E0>       \
+                                      : k_reduced_gather<TV, P, false, EPI, BJ, false>);  \
+      hipExtLaunchKernelGGL(k, grid, block, 0, st, ev0, ev1, 0, blocks, scales, einv,     \
+                            einvsc, xe, h, esite, V, n, chunk, tm, o, ee, yy,             \
+                            c0, ca, cb, done);                                            \
+    }                                                                                     \
     break;
     DC_CASE(1) DC_CASE(2) DC_CASE(3) DC_CASE(4) DC_CASE(5) DC_CASE(6) DC_CASE(7) DC_CASE(8)
 #undef DC_CASE
@@ -1754,6 +1751,7 @@ void launch_reduced_gather(Prec p, int epi, int n, int V, const void* blocks,
                            void* out, const void* e, void* y, z64 c0, z64 ca, z64 cb,
                            const int* done, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, int g5) {
   if (epi < 0 || epi > 3) throw InvalidArg("reduced epilogue must be 0..3");
+  if (g5 && epi != 0) throw InvalidArg("Gamma5 comes with the plain store only");
   if (einv && epi == 3) throw InvalidArg("the residual epilogue takes the unpreconditioned operator");
   if (!single_read_fits(p, n))
     throw InvalidArg("the single-read reduced kernels do not take this precision and block size");
