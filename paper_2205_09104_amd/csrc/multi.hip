@@ -282,12 +282,11 @@ __global__ __launch_bounds__(256, T <= 6 ? 2 : 1) void k_apply_multi_f64(MultiOp
 // k step at a time, between the products.
 // Measured (16^4, n = 48, 64 right-hand sides; FP32 matrix instructions and
 // planes in LDS before): FP32 6.72 -> 3.95 ms, FP16 blocks 6.86 -> 3.13 ms; 12
-// right-hand sides: 2.41 -> 1.83 and 2.38 -> 1.2 ms.  At 64, matrix cores 24%,
-// vector ALU (the splits) 45% busy.  Neither bounds it: with the products or the
-// splits left out it takes as long.  What is left is the traffic of a workgroup's own
-// memories: fragment reads of the block by each of four waves (a third of the
-// reads: 0.4 ms less) and the panels' way through the L1 and the strips (19 GB
-// through the L2s, 7.7 GB once each; all loads from one site's data: 0.7 ms less).
+// right-hand sides: 2.41 -> 1.83 and 2.38 -> 1.2 ms.  At 64, matrix cores 30%, vector
+// ALU (the splits) 55%, LDS 44% busy, at a clock that falls to 1.9 GHz under it.  With
+// the products or the splits left out it takes as long; a third of the fragment reads
+// of the block (by each of four waves) takes 0.4 ms less, all loads from one site's
+// data 0.7 ms (19 GB go through the L2s, 7.7 GB once each).
 // Three couplings in flight instead of one cost more occupancy than they gain
 // (n = 16, 32: 10% slower).
 
