@@ -52,8 +52,16 @@ __device__ void block_partials(double (&v)[W], double* partials) {
 // result[v] = sum_b partials[v * nparts + b]; one 64-lane wave per value.
 __device__ inline void finalize_value(const double* __restrict__ partials, int nparts,
                                       double* __restrict__ result, int v) {
+  const double* p = partials + size_t(v) * nparts;
   double s = 0.0;
-  for (int b = threadIdx.x; b < nparts; b += 64) s += partials[size_t(v) * nparts + b];
+  for (int b = threadIdx.x; b < nparts; b += 512) {   // eight loads in flight, added in order
+    double t[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) t[u] = p[min(b + 64 * u, nparts - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (b + 64 * u < nparts) s += t[u];
+  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) s += shfl_xor(s, o);
   if (threadIdx.x == 0) result[v] = s;

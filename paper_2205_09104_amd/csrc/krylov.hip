@@ -145,7 +145,7 @@ __global__ __launch_bounds__(256) void k_multidot(const cx<VR>* __restrict__ b0,
 // base + e 64 + lane.
 constexpr int kSplitWaves = 4;   // waves per workgroup (256 threads)
 
-template <typename VR>
+template <typename VR, int G>
 __device__ inline void split_sums(const cx<VR>* __restrict__ b0, int q0,
                                   const cx<VR>* __restrict__ b1, size_t N, int Q,
                                   const double* __restrict__ coef, size_t base, int lane,
@@ -157,10 +157,10 @@ __device__ inline void split_sums(const cx<VR>* __restrict__ b0, int q0,
     idx[e] = i < N ? i : N - 1;
     sr[e] = si[e] = 0.0;
   }
-  for (int qc = wave * kAxpyG; qc < Q; qc += kSplitWaves * kAxpyG) {
-    cx<VR> v[kAxpyG][kDotE];
+  for (int qc = wave * G; qc < Q; qc += kSplitWaves * G) {
+    cx<VR> v[G][kDotE];
 #pragma unroll
-    for (int t = 0; t < kAxpyG; ++t) {
+    for (int t = 0; t < G; ++t) {
       const int q = min(qc + t, Q - 1);
       const cx<VR>* p = basis_ptr(b0, q0, b1, N, q);
 #pragma unroll
@@ -168,7 +168,7 @@ __device__ inline void split_sums(const cx<VR>* __restrict__ b0, int q0,
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int t = 0; t < kAxpyG; ++t) {
+    for (int t = 0; t < G; ++t) {
       const int q = qc + t;
       const double cr = q < Q ? coef[2 * q] : 0.0, ci = q < Q ? coef[2 * q + 1] : 0.0;
 #pragma unroll
@@ -182,7 +182,7 @@ __device__ inline void split_sums(const cx<VR>* __restrict__ b0, int q0,
 }
 
 // out = (w - sum_q coef_q basis_q) sc; out may be w.  Block bx of gx (blockIdx.x / gridDim.x of a plain launch).
-template <typename VR>
+template <typename VR, int G = kAxpyG>
 __device__ __forceinline__ void multiaxpy_split_body(const cx<VR>* w, cx<VR>* out,
                                                      const cx<VR>* __restrict__ b0, int q0,
                                                      const cx<VR>* __restrict__ b1, int q1,
@@ -197,7 +197,7 @@ __device__ __forceinline__ void multiaxpy_split_body(const cx<VR>* w, cx<VR>* ou
   for (size_t base = size_t(bx) * span; base < N; base += size_t(gx) * span) {
     size_t idx[kDotE];
     double sr[kDotE], si[kDotE];
-    split_sums<VR>(b0, q0, b1, N, Q, coef, base, lane, wave, idx, sr, si);
+    split_sums<VR, G>(b0, q0, b1, N, Q, coef, base, lane, wave, idx, sr, si);
 #pragma unroll
     for (int e = 0; e < kDotE; ++e) {
       part[wave][e][0][lane] = sr[e];
@@ -367,7 +367,7 @@ __global__ __launch_bounds__(256) void k_combine1(const cx<VR>* __restrict__ b0,
   for (size_t base = size_t(blockIdx.x) * span; base < N; base += size_t(gridDim.x) * span) {
     size_t idx[kDotE];
     double sr[kDotE], si[kDotE];
-    split_sums<VR>(b0, q0, b1, N, Q, coef, base, lane, wave, idx, sr, si);
+    split_sums<VR, kAxpyG>(b0, q0, b1, N, Q, coef, base, lane, wave, idx, sr, si);
 #pragma unroll
     for (int e = 0; e < kDotE; ++e) {
       part[wave][e][0][lane] = sr[e];
@@ -934,7 +934,7 @@ __global__ __launch_bounds__(64) void k_arnoldi_finish(ArnoldiDev a, int steps, 
 // does the bookkeeping beside the update.  Three launches per step where separate
 // passes take nine, three passes over the basis where they take four, and none for
 // the norm and the scaling: 30 steps on 8^4 (FP64, n = 48) 6.85 -> 6.27 ms, where the
-// operator's applies are 4.7 ms; an odd-even GCRO-DR solve on 4^4, n = 16, 6.6 ->
+// operator's applies were 4.7 ms (5.55 with 4.2 ms of applies since); an odd-even GCRO-DR solve on 4^4, n = 16, 6.6 ->
 // 4.8 ms.  Finishing the reductions in the last workgroup to arrive was slower (7.3
 // and 5.1 ms): its fences write back and invalidate each die's L2.
 
@@ -1072,7 +1072,8 @@ struct StepEnd {
 // w = (w - [b0 b1] c) / h_{j+1,j} with the last pass's coefficients c (FOLD: nparts
 // partials per value at src, else at src itself), for the step whose first kernel
 // set the flag; workgroup 0 runs the step's bookkeeping meanwhile.
-template <typename VR, bool SPLIT, bool FOLD>
+// G: vectors per chunk of the split update (0: the flat one).
+template <typename VR, int G, bool FOLD>
 __global__ __launch_bounds__(256) void k_step_end(cx<VR>* w, const cx<VR>* __restrict__ b0, int q0,
                                                   const cx<VR>* __restrict__ b1, int q1, size_t N,
                                                   const double* __restrict__ src, int nparts,
@@ -1097,8 +1098,8 @@ __global__ __launch_bounds__(256) void k_step_end(cx<VR>* w, const cx<VR>* __res
   }
   __syncthreads();
   const int bx = int(blockIdx.x) - 1, gx = int(gridDim.x) - 1;
-  if constexpr (SPLIT)
-    multiaxpy_split_body<VR>(w, w, b0, q0, b1, q1, N, FOLD ? cf : src, 0, nullptr, inv, bx, gx);
+  if constexpr (G != 0)
+    multiaxpy_split_body<VR, G>(w, w, b0, q0, b1, q1, N, FOLD ? cf : src, 0, nullptr, inv, bx, gx);
   else
     multiaxpy_flat_body<VR>(w, w, b0, q0, b1, q1, N, FOLD ? cf : src, 0, nullptr, inv, bx, gx);
 }
@@ -1307,8 +1308,11 @@ static void gram_schmidt_t(const void* b0, int q0, const void* b1, int q1, size_
   e.kC = kC;
   e.j = j;
   const bool split = Q > kAxpyG;
-  auto k = split ? (np > 0 ? k_step_end<VR, true, true> : k_step_end<VR, true, false>)
-                 : (np > 0 ? k_step_end<VR, false, true> : k_step_end<VR, false, false>);
+  // up to 32 vectors in chunks of 8, so that all four waves have one (8^4, n = 48, FP64,
+  // 17 to 30 vectors: 18.7 -> 16.2 us)
+  auto k = !split ? (np > 0 ? k_step_end<VR, 0, true> : k_step_end<VR, 0, false>)
+           : Q <= 32 ? (np > 0 ? k_step_end<VR, 8, true> : k_step_end<VR, 8, false>)
+                     : (np > 0 ? k_step_end<VR, kAxpyG, true> : k_step_end<VR, kAxpyG, false>);
   // (the sums and the norm once per workgroup: at most two per CU)
   hipLaunchKernelGGL(k, dim3(std::min(axpy_blocks(N, split), 512u) + 1), dim3(256), 0, st, static_cast<cx<VR>*>(w), v0,
                      q0, v1, q1, N, np > 0 ? last : cres, np, e);
