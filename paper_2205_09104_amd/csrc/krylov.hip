@@ -1181,9 +1181,9 @@ void launch_finalize(const double* partials, int nvals, int nparts, double* resu
 
 // blocks per dot group: about one pass per thread, bounded by the partials
 // capacity over all groups and values
-static unsigned dot_blocks(size_t N, int values, int capacity = kRedCap) {
+static unsigned dot_blocks(size_t N, int values) {
   size_t b = (N + 256 * kDotE - 1) / (256 * kDotE);
-  const size_t cap = size_t(capacity) / size_t(values > 0 ? values : 1);
+  const size_t cap = size_t(kRedCap) / size_t(values > 0 ? values : 1);
   if (b > cap) b = cap;
   if (b > 1024) b = 1024;
   if (b < 1) b = 1;
@@ -1193,9 +1193,9 @@ static unsigned dot_blocks(size_t N, int values, int capacity = kRedCap) {
 template <typename VR, int G>
 static void multidot_g(const void* b0, int q0, const void* b1, int q1, size_t N, const void* w,
                        Reducer red, const int* done, int Q, hipStream_t st, unsigned* gx_out,
-                       int cap, int* go, int step) {
+                       int* go, int step) {
   const int gy = (Q + G - 1) / G;
-  const unsigned gx = dot_blocks(N, gy * 2 * G, cap);
+  const unsigned gx = dot_blocks(N, gy * 2 * G);
   hipLaunchKernelGGL((k_multidot<VR, G>), dim3(gx, unsigned(gy)), dim3(256), 0, st,
                      static_cast<const cx<VR>*>(b0), q0, static_cast<const cx<VR>*>(b1), q1, N,
                      static_cast<const cx<VR>*>(w), red, done, go, step);
@@ -1205,12 +1205,12 @@ static void multidot_g(const void* b0, int q0, const void* b1, int q1, size_t N,
 template <typename VR>
 static unsigned multidot_t(const void* b0, int q0, const void* b1, int q1, size_t N,
                            const void* w, Reducer red, const int* done, int Q, hipStream_t st,
-                           int cap = kRedCap, int* go = nullptr, int step = 0) {
+                           int* go = nullptr, int step = 0) {
   unsigned gx = 0;
-  if (Q <= 2) multidot_g<VR, 2>(b0, q0, b1, q1, N, w, red, done, Q, st, &gx, cap, go, step);
-  else if (Q <= 4) multidot_g<VR, 4>(b0, q0, b1, q1, N, w, red, done, Q, st, &gx, cap, go, step);
-  else if (Q <= 8) multidot_g<VR, 8>(b0, q0, b1, q1, N, w, red, done, Q, st, &gx, cap, go, step);
-  else multidot_g<VR, 16>(b0, q0, b1, q1, N, w, red, done, Q, st, &gx, cap, go, step);
+  if (Q <= 2) multidot_g<VR, 2>(b0, q0, b1, q1, N, w, red, done, Q, st, &gx, go, step);
+  else if (Q <= 4) multidot_g<VR, 4>(b0, q0, b1, q1, N, w, red, done, Q, st, &gx, go, step);
+  else if (Q <= 8) multidot_g<VR, 8>(b0, q0, b1, q1, N, w, red, done, Q, st, &gx, go, step);
+  else multidot_g<VR, 16>(b0, q0, b1, q1, N, w, red, done, Q, st, &gx, go, step);
   return gx;
 }
 
@@ -1269,21 +1269,25 @@ static void gram_schmidt_t(const void* b0, int q0, const void* b1, int q1, size_
     launch_finalize(parts, nvals, int(gx), result, a.done, st);
     return 0;
   };
-  // the second half of the partials is for the kernel that sums the first
   const double* last = red.partials;
   double* cres = res1;
-  unsigned gx = multidot_t<VR>(b0, q0, b1, q1, N, w, red, a.done, Q + 1, st, kRedCap / 2, a.go, j + 1);
+  unsigned gx = multidot_t<VR>(b0, q0, b1, q1, N, w, red, a.done, Q + 1, st, a.go, j + 1);
   DC_HIP(hipGetLastError());
   int np = settle(gx, red.partials, res1);
   if (!single_sync) {
     cres = res2;
-    double* second = red.partials + kRedCap / 2;
+    // behind the partials that the next kernel still sums (of at most kFoldQ + 1 vectors,
+    // rounded up to a group of 16)
+    constexpr int kept = 2 * (kFoldQ + 16) * kFoldParts;
+    static_assert(kept <= kRedCap / 2, "room for the second kernel's partials");
+    double* second = red.partials + (np > 0 ? kept : 0);
+    const int cap = kRedCap - (np > 0 ? kept : 0);
     last = second;
     if (Q <= kFoldQ) {
       // at most two workgroups per CU (their registers allow no more), with equal
       // numbers of tiles
       const size_t tiles = (N + 63) / 64;
-      const size_t most = std::min<size_t>(512, size_t(kRedCap / 2) / size_t(nvals));
+      const size_t most = std::min<size_t>(512, size_t(cap) / size_t(nvals));
       const size_t rounds = (tiles + most - 1) / most;
       gx = unsigned(std::max<size_t>((tiles + rounds - 1) / std::max<size_t>(rounds, 1), 1));
       auto k = np > 0 ? k_update_dot<VR, true> : k_update_dot<VR, false>;
@@ -1294,7 +1298,7 @@ static void gram_schmidt_t(const void* b0, int q0, const void* b1, int q1, size_
       // more vectors than a workgroup's registers hold: the update and its dots
       // each read the basis
       launch_multiaxpy(p, w, b0, q0, b1, q1, N, res1, 0, red, nullptr, a.done, st);
-      gx = multidot_t<VR>(b0, q0, b1, q1, N, w, Reducer{second}, a.done, Q + 1, st, kRedCap / 2);
+      gx = multidot_t<VR>(b0, q0, b1, q1, N, w, red, a.done, Q + 1, st);
       DC_HIP(hipGetLastError());
     }
     np = settle(gx, second, res2);
@@ -1314,8 +1318,8 @@ static void gram_schmidt_t(const void* b0, int q0, const void* b1, int q1, size_
            : Q <= 32 ? (np > 0 ? k_step_end<VR, 8, true> : k_step_end<VR, 8, false>)
                      : (np > 0 ? k_step_end<VR, kAxpyG, true> : k_step_end<VR, kAxpyG, false>);
   // (the sums and the norm once per workgroup: at most two per CU)
-  hipLaunchKernelGGL(k, dim3(std::min(axpy_blocks(N, split), 512u) + 1), dim3(256), 0, st, static_cast<cx<VR>*>(w), v0,
-                     q0, v1, q1, N, np > 0 ? last : cres, np, e);
+  hipLaunchKernelGGL(k, dim3(std::min(axpy_blocks(N, split), 512u) + 1), dim3(256), 0, st,
+                     static_cast<cx<VR>*>(w), v0, q0, v1, q1, N, np > 0 ? last : cres, np, e);
   DC_HIP(hipGetLastError());
 }
 
