@@ -181,7 +181,8 @@ __device__ inline void split_sums(const cx<VR>* __restrict__ b0, int q0,
   }
 }
 
-// out = (w - sum_q coef_q basis_q) sc; out may be w.  Block bx of gx (blockIdx.x / gridDim.x of a plain launch).
+// out = (w - sum_q coef_q basis_q) sc; out may be w.  Block bx of gx (blockIdx.x /
+// gridDim.x of a plain launch).
 template <typename VR, int G = kAxpyG>
 __device__ __forceinline__ void multiaxpy_split_body(const cx<VR>* w, cx<VR>* out,
                                                      const cx<VR>* __restrict__ b0, int q0,
@@ -933,10 +934,11 @@ __global__ __launch_bounds__(64) void k_arnoldi_finish(ArnoldiDev a, int steps, 
 // kernel that applies the first's, and one extra workgroup of the last kernel
 // does the bookkeeping beside the update.  Three launches per step where separate
 // passes take nine, three passes over the basis where they take four, and none for
-// the norm and the scaling: 30 steps on 8^4 (FP64, n = 48) 6.85 -> 6.27 ms, where the
-// operator's applies were 4.7 ms (5.55 with 4.2 ms of applies since); an odd-even GCRO-DR solve on 4^4, n = 16, 6.6 ->
-// 4.8 ms.  Finishing the reductions in the last workgroup to arrive was slower (7.3
-// and 5.1 ms): its fences write back and invalidate each die's L2.
+// the norm and the scaling: 30 steps on 8^4 (FP64, n = 48) 6.85 -> 6.27 ms, of them
+// 4.7 ms in the operator's applies (5.55 ms with 4.2 ms of applies since); an odd-even
+// GCRO-DR solve on 4^4, n = 16, 6.6 -> 4.8 ms; 120 steps on 16^4, n = 16 140.8 -> 127.9
+// ms.  Finishing the reductions in the last workgroup to arrive was slower (7.3 and
+// 5.1 ms): its fences write back and invalidate each die's L2.
 
 constexpr int kFoldQ = 64;        // vectors of the basis that k_update_dot holds in registers
 // Partials per value that the next kernel sums itself; more are summed by a launch of
