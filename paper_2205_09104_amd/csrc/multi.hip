@@ -96,6 +96,46 @@ __device__ inline MultiOpDesc op_of(const MultiOps& ops, unsigned item) {
 // ms, 8^4, n = 16, 32: 84 -> 67 us.  Matrix cores 46% busy at 12 right-hand sides;
 // operands loaded straight from the tiled block to registers cost one address
 // per lane and ran at 312 us.
+
+// Where a lane of k_apply_multi_f64 finds its entry of row tile rt in step t of its
+// wave: byte offsets in the block's LDS buffer.
+template <int T>
+struct F64Entry {
+  static constexpr int BYTES = T * T * 1024;              // a block: T x T units of 64 entries
+  static constexpr int RT = (T + 1) / 2, NS = 2 * T, SPW = (NS + 3) / 4;
+  __host__ __device__ static constexpr int unit(bool trans, int a, int c) {
+    return (trans ? c * T + a : a * T + c) * 1024;
+  }
+  // the lane's part: row lr (lc) = sub of unit row par, column kk of unit column c0
+  __host__ __device__ static constexpr int lane_part(bool trans, int wave, int lane) {
+    const int sub = lane & 7, par = (lane >> 3) & 1, kk = 4 * (wave & 1) + (lane >> 4);
+    return unit(trans, par, wave >> 1) + (trans ? kk * 8 + (sub ^ kk) : sub * 8 + (kk ^ sub)) * 16;
+  }
+  // an odd T has no second unit row in its last tile
+  __host__ __device__ static constexpr bool missing(int rt, int lane) {
+    return T % 2 != 0 && rt == RT - 1 && ((lane >> 3) & 1) != 0;
+  }
+  // the uniform part; lanes without a unit row read the one before it (and put zero)
+  __host__ __device__ static constexpr int step_part(bool trans, int rt, int t, bool none) {
+    return unit(trans, 2 * rt - (none ? 1 : 0), 2 * t);
+  }
+  static constexpr bool inside() {
+    for (int trans = 0; trans < 2; ++trans)
+      for (int wave = 0; wave < 4; ++wave)
+        for (int lane = 0; lane < 64; ++lane)
+          for (int t = 0; wave + 4 * t < NS; ++t)
+            for (int rt = 0; rt < RT; ++rt) {
+              const int at = lane_part(trans, wave, lane) + step_part(trans, rt, t, missing(rt, lane));
+              if (at < 0 || at + 16 > BYTES) return false;
+            }
+    return true;
+  }
+};
+static_assert(F64Entry<1>::inside() && F64Entry<2>::inside() && F64Entry<3>::inside() &&
+                  F64Entry<4>::inside() && F64Entry<5>::inside() && F64Entry<6>::inside() &&
+                  F64Entry<7>::inside() && F64Entry<8>::inside(),
+              "every read stays in its block's buffer");
+
 template <int T, int RB>
 __global__ __launch_bounds__(256, T <= 6 ? 2 : 1) void k_apply_multi_f64(MultiOps ops, unsigned sites,
                                                                         int chunk) {
@@ -127,9 +167,8 @@ __global__ __launch_bounds__(256, T <= 6 ? 2 : 1) void k_apply_multi_f64(MultiOp
   // step t of this wave: s = wave + 4 t = 2 c + h, columns (4 h + lk) T + c
   const int kk = 4 * (wave & 1) + lk, c0 = wave >> 1;
   const int sub = l16 & 7, par = l16 >> 3;   // row of a tile: (lr or lc) = sub, a (b) = 2 rt + par
-  // LDS offsets of the lane's entry: unit a T + c, or transposed c T + a
-  const int at_f = (par * T + c0) * 1024 + (sub * 8 + (kk ^ sub)) * 16;
-  const int at_t = (c0 * T + par) * 1024 + (kk * 8 + (sub ^ kk)) * 16;
+  using At = F64Entry<T>;
+  const int at_f = At::lane_part(false, wave, lane), at_t = At::lane_part(true, wave, lane);
 
   auto load_block = [&](int blk, int buf) {
     const int lr = lane >> 3, lc = lane & 7;
@@ -197,10 +236,8 @@ __global__ __launch_bounds__(256, T <= 6 ? 2 : 1) void k_apply_multi_f64(MultiOp
       if (NS % 4 != 0 && wave + 4 * t >= NS) continue;
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
-        // an odd T has no second unit row in its last tile: those rows are zero
-        const bool none = T % 2 != 0 && rt == RT - 1 && par != 0;
-        const int at = trans ? (2 * t * T + 2 * rt) * 1024 : (2 * rt * T + 2 * t) * 1024;
-        d2 z = *reinterpret_cast<const d2*>(base + (none ? 0 : at));
+        const bool none = At::missing(rt, lane);
+        d2 z = *reinterpret_cast<const d2*>(base + At::step_part(trans, rt, t, none));
         if (none) z = d2{0.0, 0.0};
         const uint32_t mi = trans && sub * T + 2 * rt + par >= half ? 0x80000000u : 0u;
         const double ar = flip(z.x, mi), ai = flip(z.y, trans ? mi ^ 0x80000000u : 0u);

@@ -220,3 +220,31 @@ def test_apply_routes(dims, ntv, mu):
         assert rel(gop.apply(x32, prec=prec, adjoint=True).cpu().numpy(), refa) <= (
             2e-6 if prec == "f32" else 3e-3), prec
     gop.close()
+
+
+# Multi-right-hand-side apply in FP64: tiles T = 1..8 (odd ones lack the second unit row of
+# their last tile; at T = 1 that is the whole tile but one), full and ragged, uneven step
+# counts per wave, both right-hand-side tiles.  The bound is that of the oracle comparison
+# of this kernel; a tile changes no bit of the result.
+@pytest.mark.parametrize("dims,ntv,R", [((5, 3, 2, 2), 1, 1), ((4, 2, 2, 2), 4, 5),
+                                        ((3, 2, 2, 3), 8, 16), ((2, 3, 2, 2), 11, 17),
+                                        ((2, 2, 3, 2), 12, 15), ((4, 2, 1, 2), 16, 33),
+                                        ((2, 2, 2, 2), 19, 12), ((2, 2, 2, 2), 20, 40),
+                                        ((2, 2, 2, 1), 27, 31), ((2, 1, 2, 2), 28, 16),
+                                        ((2, 2, 1, 2), 31, 20)])
+def test_multi_f64_tiles(dims, ntv, R):
+    import paper_2205_09104_amd as dc
+    gop, oop = make_pair(dims, ntv, 3.0, mu=0.2)
+    X = torch.stack([rand_vec(oop.V, oop.n, 37, r) for r in range(R)]).cuda()
+    for adj in (False, True):
+        ref = torch.stack([gop.apply(x, adjoint=adj) for x in X])
+        out = []
+        try:
+            for tile in (16, 32):
+                dc.set_multi_tile_mode(tile)
+                out.append(gop.apply_multi(X, adjoint=adj))
+        finally:
+            dc.set_multi_tile_mode(0)
+        log(f"  multi f64 {dims} n {oop.n} R {R} adjoint {adj}: {_rel(out[0], ref):.1e}")
+        assert _rel(out[0], ref) <= 1e-13 and torch.equal(out[0], out[1])
+    gop.close()
