@@ -274,9 +274,10 @@ int dc_apply_reduced_bj(dc_op_t op, int32_t prec, const void* in, void* out, voi
 
 /* Multi-right-hand-side apply (MFMA): out_r = D_c in_r (adjoint = 0) or
  * D_c^H in_r (adjoint = 1) for r < n_rhs; in, out device [n_rhs][V][n],
- * complex128 for DC_PREC_F64 (FP64 MFMA) and complex64 otherwise (scaled FP16
- * pieces on the FP16 matrix cores, two per FP32 value, accumulated in FP32; the
- * result is FP32-accurate for the stored blocks).  Each block times an n x n_rhs
+ * complex128 for DC_PREC_F64 (FP64 MFMA) and complex64 otherwise (an FP32 value is the
+ * sum of three BF16 pieces, a product of two the six leading products of their pieces on
+ * the BF16 matrix cores, accumulated in FP32: each product is held to one FP32
+ * rounding, whatever the sizes of the other entries).  Each block times an n x n_rhs
  * panel is a dense complex contraction (the same operator as dc_apply, one
  * launch for all right-hand sides).  in and out must not overlap. */
 int dc_apply_multi(dc_op_t op, int32_t prec, int32_t adjoint, int32_t n_rhs, const void* in,

@@ -3,6 +3,7 @@
 #include "device.hpp"
 
 #include <algorithm>
+#include <cfloat>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -21,8 +22,8 @@ namespace {
 // stored forward block transposed.  Every stored block is read once per site that uses it
 // (9 block reads per site).
 
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef __bf16 b8 __attribute__((ext_vector_type(8)));
+typedef __bf16 b2 __attribute__((ext_vector_type(2)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
@@ -296,60 +297,67 @@ __global__ __launch_bounds__(256, T <= 6 ? 2 : 1) void k_apply_multi_f64(MultiOp
   }
 }
 
-// ---- FP32 vectors: FP16 pieces on the FP16 matrix cores
-// The FP32 matrix instructions run at 1/16 of the FP16 rate.  An FP32 number
-// scaled by a power of two is the sum of two FP16 numbers, h = fp16(x) and l =
-// fp16(x - h), to 2^-24 of its magnitude, so a product of two is h h' + h l' + l h'
-// to about its own FP32 rounding error (the dropped l l' is below 2^-24 of it):
-// three FP16 products with FP32 accumulation.  FP16-stored blocks are one exact
-// piece: two products.  Scales: each block by a power of two of its largest
-// entry (kept at build time), each right-hand side's n entries at a source site
-// by one of theirs, both to [2^14, 2^15), undone in FP32 on the coupling's
-// accumulators; entries far below the largest keep 2^-39 of it.  Error against
-// 64 bits, 16^4, n = 48, 64 right-hand sides: 1.2e-7 (FP32 matrix instructions
-// with three real products per complex one: 6.3e-7).
+// ---- FP32 vectors: BF16 pieces on the BF16 matrix cores
+// The FP32 matrix instructions run at 1/16 of the BF16 rate.  A BF16 number has the
+// exponents of an FP32 one and 8 of its 24 significant bits, so an FP32 number is the
+// sum of three, x = x1 + x2 + x3, x1 = bf16(x), x2 = bf16(x - x1), x3 the rest, exactly
+// (|x2| <= 2^-8, |x3| <= 2^-17 of x's binade), and an entry keeps its own precision
+// whatever the others' sizes are.  A product of two is six products of pieces, a1 x1 +
+// (a1 x2 + a2 x1) + (a1 x3 + a2 x2 + a3 x1): what is dropped is at most 2^-24 of it, the
+// bound of an FP32 rounding.  A code of an FP16-stored block (11 bits) is two pieces, and
+// its products five.  The sums are in FP32, as the results are.
+// Pieces below 2^-126 would lose bits, and products of an FP16 block's codes, which are
+// without its scale, can overflow where the result does not.  So an FP32 block (by
+// its largest entry, kept at build time) and a right-hand side's n entries at a source
+// site are moved by 2^40 where their largest is below 2^-64, by 2^-40 where it is 2^64 or
+// more, and the products are multiplied by what undoes both and an FP16 block's scale:
+// only what overflows in the result overflows.  Next to a largest entry of 2^-64 or
+// more, entries below 2^-110 are held to 2^-133.
 // Layout: complex values stay interleaved, (re, im) pairs are two k entries:
 // Re = (ar, ai) . (pr, -pi), Im = (ar, ai) . (pi, pr), on 16x16x32 tiles (16
 // complex columns per step).  One workgroup per site and RB right-hand sides:
 // its four waves take the RB / 16 column tiles, and the row tiles where there
-// are fewer.  The couplings' blocks go through LDS as FP16 pairs (double
-// buffered, one barrier per coupling, rows padded to an odd number of 16-byte
-// units: conflict-free fragment reads); the panels go from memory to the wave
+// are fewer.  The couplings' blocks go through LDS as BF16 pairs, a plane per piece
+// (rows padded to an odd number of 16-byte units: conflict-free fragment reads); the panels go from memory to the wave
 // that multiplies them, which holds its fragments in registers and splits them one
-// k step at a time, between the products.
-// Measured (16^4, n = 48, 64 right-hand sides; FP32 matrix instructions and
-// planes in LDS before): FP32 6.72 -> 3.95 ms, FP16 blocks 6.86 -> 3.13 ms; 12
-// right-hand sides: 2.41 -> 1.83 and 2.38 -> 1.2 ms.  At 64, matrix cores 30%, vector
-// ALU (the splits) 55%, LDS 44% busy, at a clock that falls to 1.9 GHz under it.  With
-// the products or the splits left out it takes as long; a third of the fragment reads
-// of the block (by each of four waves) takes 0.4 ms less, all loads from one site's
-// data 0.7 ms (19 GB go through the L2s, 7.7 GB once each).
+// k step at a time, between the products.  A step's products are summed small ones
+// first, from zero, and then added.
+// Measured (16^4, n = 48, 64 right-hand sides; FP32 matrix instructions, three real products
+// per complex one, and planes in LDS before): FP32 6.70 -> 5.18 ms, FP16 blocks 6.87 -> 4.14
+// ms; 12 right-hand sides: 2.29 -> 2.21 and 2.38 -> 1.61 ms.  At 64 in FP32, matrix cores 44%,
+// vector ALU (the splits) 64%, LDS 43% busy, at a clock that falls to 1.9 GHz under it.
+// Error, each entry against the sum of the magnitudes that enter it, n = 48: 4e-8 to
+// 1.6e-7 over evenly sized and graded operands (2e-7 to 5e-7 before).  Two FP16 pieces with a
+// scale per block and column take three products and 3.7 ms, but hold entries far
+// below the largest to too few bits: they lost rows and columns of graded blocks.
 // Three couplings in flight instead of one cost more occupancy than they gain
 // (n = 16, 32: 10% slower).
 
-// Power-of-two scale that takes a largest magnitude m to [2^14, 2^15), and its
-// inverse; both stay normal numbers (m below 2^-112 scales to less, infinite
-// and NaN m leave finite factors, so they reach the result).
+// Power of two that brings a largest magnitude m towards 1 where it is near an end of
+// the range of the exponents, and its inverse.
 __device__ inline void pow2_scale(float m, float& up, float& down) {
-  const uint32_t e = max((__float_as_uint(m) >> 23) & 255u, 15u);   // biased exponent
-  up = __uint_as_float((268u - e) << 23);
-  down = __uint_as_float((e - 14u) << 23);
+  const uint32_t e = (__float_as_uint(m) >> 23) & 255u;   // biased exponent
+  up = e < 63u ? 0x1p40f : e > 190u ? 0x1p-40f : 1.f;
+  down = e < 63u ? 0x1p-40f : e > 190u ? 0x1p40f : 1.f;
 }
 
-// FP16 pieces of a scaled complex value, packed (re low, im high).
-__device__ inline void split_pair(float re, float im, uint32_t& hi, uint32_t& lo) {
-  const h2 h = __builtin_convertvector(f2{re, im}, h2);
-  const h2 l = __builtin_convertvector(f2{re - float(h.x), im - float(h.y)}, h2);
-  hi = __builtin_bit_cast(uint32_t, h);
-  lo = __builtin_bit_cast(uint32_t, l);
+// The leading N BF16 pieces of a complex value, each packed (re low, im high).
+template <int N>
+__device__ inline void split_pair(float re, float im, uint32_t (&p)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    p[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{re, im}, b2));
+    re -= __uint_as_float(p[i] << 16);
+    im -= __uint_as_float(p[i] & 0xffff0000u);
+  }
 }
 
 // Waves per column tile: they share its k steps, every one over all row tiles, so
 // no panel entry is split twice; small blocks that leave waves over put several
 // sites into a workgroup.  (16^4, n = 48, 12 right-hand sides, against waves that
-// share the row tiles and each split the whole panel: FP32 2.43 -> 1.82 ms, FP16
-// blocks 1.84 -> 1.19; n = 16, 32 on 8^4: 54 -> 39 us.)
-template <int T, int RB>
+// share the row tiles and each split the whole panel, with two pieces per entry: FP32 2.43
+// -> 1.82 ms, FP16 blocks 1.84 -> 1.19; n = 16, 32 on 8^4: 54 -> 39 us.)
+template <int T, int P, int RB>
 struct SplitShape {
   static constexpr int NP = (8 * T + 15) / 16 * 16;   // block edge padded to whole tiles
   static constexpr int RT = NP / 16, KS = NP / 16;    // row tiles, k steps of 16 complex columns
@@ -360,24 +368,31 @@ struct SplitShape {
   // Panels of more than 16 columns come in 128-byte segments and turn into fragments
   // through LDS: a fragment's own loads touch 64 cache lines each, and their look-ups
   // bounded the kernel.  16 columns (bound by the blocks) are loaded as fragments.
-  // 16^4, n = 48, FP32, fragments / segments: 64 columns 4.6 / 3.95 ms, 32 5.6 / 5.1,
-  // 16 1.84 / 1.91.
+  // 16^4, n = 48, fragments / segments: 64 columns FP32 5.40 / 5.18 ms, FP16 blocks 4.56 /
+  // 4.14, 32 6.54 / 6.50, 16 2.21 / 2.23.
   static constexpr bool STRIP = CT > 1;
+  // Block buffers: two write the next block beside the products (one barrier per
+  // coupling), one leaves room for more workgroups.  Two buffers / one, 16^4, n = 48, 12
+  // right-hand sides, ms: FP32 (three pieces) 3.06 / 2.24, FP16 blocks (two) 1.65 / 1.91;
+  // 64: 5.43 / 5.25 and 4.26 / 4.39; 8^4, n = 64, 64 in FP32: 0.75 / 0.58.
+  static constexpr int NBUF = P == P32 ? 1 : 2;
   // workgroups per CU that the registers are held to (three: 168, T = 6 at 64 columns
-  // spills two; against two there: 3.95 / 4.18 ms)
-  static constexpr int WAVES = T > 6 ? 2 : STRIP ? 3 : 4;
+  // spills two to four; against two there: 5.26 / 5.48 ms, FP16 blocks 4.22 / 4.47; four at
+  // 16 columns spill more: 2.64 / 2.24 ms)
+  static constexpr int WAVES = T > 6 ? 2 : 3;
 };
 
 template <int T, int P, int RB>
-__global__ __launch_bounds__(256, (SplitShape<T, RB>::WAVES)) void k_apply_multi_split(
+__global__ __launch_bounds__(256, (SplitShape<T, P, RB>::WAVES)) void k_apply_multi_split(
     MultiOps ops, unsigned sites, int chunk) {
-  using Sh = SplitShape<T, RB>;
+  using Sh = SplitShape<T, P, RB>;
   constexpr int NP = Sh::NP, RT = Sh::RT, KS = Sh::KS, CT = Sh::CT, KG = Sh::KG, KSW = Sh::KSW;
   constexpr int WPS = Sh::WPS, SPB = Sh::SPB;
-  constexpr int PIECES = (P == P32) ? 2 : 1;      // FP16 pieces of a block
+  constexpr int PIECES = (P == P32) ? 3 : 2;      // BF16 pieces of a block entry
+  constexpr int NBUF = Sh::NBUF;                  // buffers of a block
   constexpr int LDA = (NP + 4) * 4;               // bytes of an LDS row (NP pairs + padding)
   constexpr int PLANE = NP * LDA + 16;            // + a word that takes padding entries
-  constexpr int SLDS = 2 * PIECES * PLANE;        // bytes of a site
+  constexpr int SLDS = NBUF * PIECES * PLANE;     // bytes of a site
   constexpr int TT = T * T;
   constexpr int EPL = (P == P32) ? 2 : 4;         // block entries per 16-byte unit
   constexpr int UPL = (TT + EPL - 1) / EPL;       // units per lane of a block
@@ -454,8 +469,16 @@ __global__ __launch_bounds__(256, (SplitShape<T, RB>::WAVES)) void k_apply_multi
       for (int q = 0; q < 2; ++q) braw[t][q] = *(gptr<f4>)(xq[q] + x + joff[t][q]);
   };
   auto store_block = [&](unsigned char* buf, float scale, bool trans) {
-    float up = 1.f, down = 1.f;
-    if (P == P32) pow2_scale(scale, up, down);
+    if constexpr (P == P32) {
+      float up, down;
+      pow2_scale(scale, up, down);
+      if (up != 1.f) {
+#pragma unroll
+        for (int s = 0; s < MU; ++s)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) araw[s][q] = __float_as_uint(__uint_as_float(araw[s][q]) * up);
+      }
+    }
     // transposed: Gamma5 B^H Gamma5 = g_i g_j conj(B[j][i]); the masks negate
     // the imaginary (+) or the real part (-) of a packed pair
     unsigned char* base = buf + (trans ? lbase_t : lbase);
@@ -467,21 +490,17 @@ __global__ __launch_bounds__(256, (SplitShape<T, RB>::WAVES)) void k_apply_multi
       for (int q = 0; q < EPL; ++q) {
         const int e = k * EPL + q;
         const int a = e / T, b = e - a * T;
-        uint32_t hi, lo = 0;
+        uint32_t p[PIECES];
         if constexpr (P == P32)
-          split_pair(__uint_as_float(araw[s][2 * q]) * up, __uint_as_float(araw[s][2 * q + 1]) * up,
-                     hi, lo);
+          split_pair(__uint_as_float(araw[s][2 * q]), __uint_as_float(araw[s][2 * q + 1]), p);
         else
-          hi = araw[s][q];
+          split_pair(lo_h(araw[s][q]), hi_h(araw[s][q]), p);
         unsigned char* at = base + (trans ? b * LDA + a * 4 : a * LDA + b * 4);
         if (TT % EPL != 0 && e >= TT) at = buf + NP * LDA;
-        if (trans) {
-          const uint32_t m = (lr * T + a < half) == (lc * T + b < half) ? 0x80000000u : 0x00008000u;
-          hi ^= m;
-          lo ^= m;
-        }
-        *reinterpret_cast<uint32_t*>(at) = hi;
-        if (PIECES == 2) *reinterpret_cast<uint32_t*>(at + PLANE) = lo;
+        const uint32_t m = (lr * T + a < half) == (lc * T + b < half) ? 0x80000000u : 0x00008000u;
+#pragma unroll
+        for (int i = 0; i < PIECES; ++i)
+          *reinterpret_cast<uint32_t*>(at + i * PLANE) = trans ? p[i] ^ m : p[i];
       }
     }
   };
@@ -509,13 +528,20 @@ __global__ __launch_bounds__(256, (SplitShape<T, RB>::WAVES)) void k_apply_multi
       *reinterpret_cast<u4*>(lds_all + t) = u4{0, 0, 0, 0};
     __syncthreads();
   }
-  store_block(lds, scale_of(0), false);
-  load_block(block_of(1));
+  if (NBUF == 2) {
+    store_block(lds, scale_of(0), false);
+    load_block(block_of(1));
+  }
 #pragma unroll 1
   for (int c = 0; c < 9; ++c) {
-    unsigned char* buf = lds + (c & 1) * (PIECES * PLANE);
+    unsigned char* buf = lds + (NBUF == 2 ? (c & 1) * (PIECES * PLANE) : 0);
+    if (NBUF == 1) {
+      if (c > 0) __syncthreads();   // the products of the coupling before are done
+      store_block(buf, scale_of(c), coupling(c) >= 5);
+      if (c < 8) load_block(block_of(c + 1));
+    }
     __syncthreads();   // buf is complete, and the other buffer's products are done
-    // this coupling's panel -> scaled FP16 fragments (LDS keeps the order of a wave's
+    // this coupling's panel as fragments (LDS keeps the order of a wave's
     // accesses to its strip)
     f4 fr[KSW][2];
 #pragma unroll
@@ -542,75 +568,87 @@ __global__ __launch_bounds__(256, (SplitShape<T, RB>::WAVES)) void k_apply_multi
         mx = fmaxf(fmaxf(mx, fabsf(fr[t][q].x)), fabsf(fr[t][q].y));
         mx = fmaxf(fmaxf(mx, fabsf(fr[t][q].z)), fabsf(fr[t][q].w));
       }
-    mx = fmaxf(mx, shfl_xor(mx, 16));
-    mx = fmaxf(mx, shfl_xor(mx, 32));
-    float up, down;
-    pow2_scale(mx, up, down);
+    // no factor where each lane's largest entry is zero or in the range that needs none
+    float down = 1.f;
+    if (__builtin_amdgcn_ballot_w64(mx != 0.f && !(mx >= 0x1p-64f && mx < 0x1p64f)) != 0) {
+      mx = fmaxf(mx, shfl_xor(mx, 16));
+      mx = fmaxf(mx, shfl_xor(mx, 32));
+      float up;
+      pow2_scale(mx, up, down);
+#pragma unroll
+      for (int t = 0; t < KSW; ++t)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) fr[t][q] *= up;
+    }
+    if (g5in) {
+#pragma unroll
+      for (int t = 0; t < KSW; ++t)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int j = 16 * (kg + KG * t) + 4 * lk + 2 * q;
+          if (j >= half) fr[t][q].xy = -fr[t][q].xy;
+          if (j + 1 >= half) fr[t][q].zw = -fr[t][q].zw;
+        }
+    }
     float fblk = scale_of(c);
     if (P == P32) {
       float u;
       pow2_scale(fblk, u, fblk);
     }
     if (c + 1 < 9) load_panel(source(c + 1));
-    // the next panel and block are in flight, and the next block's pieces are
-    // written, while this coupling multiplies
-    if (c + 1 < 9) {
+    // the next panel and block are in flight (with two buffers, the next block's pieces
+    // are written too) while this coupling multiplies
+    if (NBUF == 2 && c + 1 < 9) {
       unsigned char* nb = lds + ((c + 1) & 1) * (PIECES * PLANE);
       if (coupling(c + 1) < 5) store_block(nb, scale_of(c + 1), false);
       else store_block(nb, scale_of(c + 1), true);
       if (c + 2 < 9) load_block(block_of(c + 2));
     }
-    f4 are[RT], aim[RT];
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) are[rt] = aim[rt] = f4{0.f, 0.f, 0.f, 0.f};
+    // both factors undone in one: what would overflow here overflows in the result
+    const float f = fminf(fblk * down, FLT_MAX);
 #pragma unroll
     for (int t = 0; t < KSW; ++t) {
       if (KS % KG != 0 && kg + KG * t >= KS) continue;
-      u4 bh, bl, bhr, blr;   // (pi, pr) pairs: the Im operand; (pr, -pi): swapped, high half negated
+      // pieces as (pi, pr) pairs, the Im operand, and (pr, -pi), the Re operand: swapped,
+      // high half negated
+      u4 bi[3], br[3];
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
-        float u0 = up, u1 = up;
-        if (g5in) {
-          const int j = 16 * (kg + KG * t) + 4 * lk + 2 * q;
-          u0 = j < half ? up : -up;
-          u1 = j + 1 < half ? up : -up;
-        }
         const f4 z = fr[t][q];
-        uint32_t h[2], l[2];
-        split_pair(z.y * u0, z.x * u0, h[0], l[0]);
-        split_pair(z.w * u1, z.z * u1, h[1], l[1]);
+        uint32_t h[2][3];
+        split_pair(z.y, z.x, h[0]);
+        split_pair(z.w, z.z, h[1]);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          bh[2 * q + i] = h[i];
-          bl[2 * q + i] = l[i];
-          bhr[2 * q + i] = __builtin_amdgcn_alignbit(h[i], h[i], 16) ^ 0x80000000u;
-          blr[2 * q + i] = __builtin_amdgcn_alignbit(l[i], l[i], 16) ^ 0x80000000u;
-        }
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            bi[k][2 * q + i] = h[i][k];
+            br[k][2 * q + i] = __builtin_amdgcn_alignbit(h[i][k], h[i][k], 16) ^ 0x80000000u;
+          }
       }
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
-        const unsigned char* row = buf + (rt * 16 + l16) * LDA + lk * 16 + kg * 64;
-        const h8 ah = *reinterpret_cast<const h8*>(row + t * KG * 64);
+        const unsigned char* row = buf + (rt * 16 + l16) * LDA + lk * 16 + kg * 64 + t * KG * 64;
+        f4 re = {0.f, 0.f, 0.f, 0.f}, im = re;
+        auto mul = [&](b8 a, int k) {
+          re = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(b8, br[k]), re, 0, 0, 0);
+          im = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(b8, bi[k]), im, 0, 0, 0);
+        };
         // small products first
-        are[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, __builtin_bit_cast(h8, blr), are[rt], 0, 0, 0);
-        aim[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, __builtin_bit_cast(h8, bl), aim[rt], 0, 0, 0);
-        if constexpr (PIECES == 2) {
-          const h8 al = *reinterpret_cast<const h8*>(row + PLANE + t * KG * 64);
-          are[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, __builtin_bit_cast(h8, bhr), are[rt], 0, 0, 0);
-          aim[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, __builtin_bit_cast(h8, bh), aim[rt], 0, 0, 0);
+        const b8 a1 = *reinterpret_cast<const b8*>(row), a2 = *reinterpret_cast<const b8*>(row + PLANE);
+        if constexpr (PIECES == 3) mul(*reinterpret_cast<const b8*>(row + 2 * PLANE), 0);
+        mul(a2, 1);
+        mul(a1, 2);
+        mul(a2, 0);
+        mul(a1, 1);
+        mul(a1, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          tre[rt][q] = fmaf(re[q], f, tre[rt][q]);
+          tim[rt][q] = fmaf(im[q], f, tim[rt][q]);
         }
-        are[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, __builtin_bit_cast(h8, bhr), are[rt], 0, 0, 0);
-        aim[rt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, __builtin_bit_cast(h8, bh), aim[rt], 0, 0, 0);
       }
     }
-    // scales undone in FP32: the column's own, then the block's
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        tre[rt][q] = fmaf(are[rt][q] * down, fblk, tre[rt][q]);
-        tim[rt][q] = fmaf(aim[rt][q] * down, fblk, tim[rt][q]);
-      }
   }
   // the k shares of a column tile added in wave order
   if (KG > 1) {
@@ -674,7 +712,7 @@ static int multi_np(int n) { return (n + 15) / 16 * 16; }
 
 template <int T, int P, int RB>
 static void split_launch(const MultiOps& ops, unsigned sites, int rmax, hipStream_t st) {
-  constexpr unsigned spb = SplitShape<T, RB>::SPB;
+  constexpr unsigned spb = SplitShape<T, P, RB>::SPB;
   const int chunk = int(((sites + spb - 1) / spb + 7) / 8);
   const unsigned rtiles = unsigned((rmax + RB - 1) / RB);
   hipLaunchKernelGGL((k_apply_multi_split<T, P, RB>), dim3(unsigned(chunk) * 8u, rtiles),

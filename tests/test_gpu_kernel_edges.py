@@ -248,3 +248,128 @@ def test_multi_f64_tiles(dims, ntv, R):
         log(f"  multi f64 {dims} n {oop.n} R {R} adjoint {adj}: {_rel(out[0], ref):.1e}")
         assert _rel(out[0], ref) <= 1e-13 and torch.equal(out[0], out[1])
     gop.close()
+
+
+# Multi-right-hand-side apply of FP32 vectors on operands whose entries are not of one size:
+# blocks with graded rows, with graded columns and the vectors graded the other way, block
+# diagonal with vectors graded over its parts, near-equal operands whose piece errors add
+# up, and magnitudes towards both ends of FP32.  All inputs are stored exactly in every
+# precision tested, so the reference is 64-bit arithmetic on the same numbers, and the error
+# of every single entry is held against the sum of the magnitudes that enter it: 2e-6 of it,
+# the normwise bound of the oracle comparison (each product is held to one FP32 rounding,
+# 6e-8, and a few dozen rounded sums follow).
+def _graded(kind, prec, V, n, R, rng):
+    import numpy as np
+
+    def mantissa(*shape):   # 9 significant bits: an FP16 code, also times 2^-13
+        def real():
+            return rng.integers(256, 513, shape) / 512.0 * rng.choice([-1.0, 1.0], shape)
+        return real() + 1j * real()
+
+    def full(*shape):
+        return (rng.normal(size=shape) + 1j * rng.normal(size=shape)).astype(np.complex64).astype(
+            np.complex128)
+
+    e = np.arange(n) / (n - 1)
+    half = prec == "f16s"
+    M = mantissa(V, 5, n, n) if half else full(V, 5, n, n)
+    X = full(R, V, n)
+
+    def pow2(t):
+        return 2.0 ** np.round(t)
+
+    deep = 13 if half else 40   # FP16 codes hold a block's entries over 2^14
+    if kind == "rows":
+        M *= pow2(-deep * e)[:, None]   # self blocks only: a hop also acts transposed
+        M[:, 1:] = 0
+    elif kind == "columns":
+        M *= pow2(-deep * e)[None, :]
+        X *= pow2(deep * e)
+    elif kind == "parts":
+        M[..., : n // 2, n // 2:] = 0
+        M[..., n // 2:, : n // 2] = 0
+        X[..., n // 2:] *= 2.0 ** -40
+    elif kind == "near one":
+        M[:] = 1 + 2.0 ** -(9 if half else 11)
+        X = np.full((R, V, n), 1 + 2.0 ** -11 + 2.0 ** -23 + 0j)
+    else:
+        block, vec = kind
+        M *= 2.0 ** block
+        X *= (2.0 ** np.linspace(vec - 8, vec, R).round())[:, None, None]
+    if half and not isinstance(kind, tuple) and kind != "near one":
+        M[:, :1 if kind == "rows" else 5, 0, 0] = 1 + 0.5j   # the block's scale: a power of two, so codes are exact
+    elif half and isinstance(kind, tuple):
+        M[..., 0, 0] = 2.0 ** kind[0]
+    elif half:
+        M[..., 0, 0] = 2.0
+    return M, X.astype(np.complex64).astype(np.complex128)
+
+
+@pytest.mark.parametrize("prec", ["f32", "f16s"])
+@pytest.mark.parametrize("kind", ["rows", "columns", "parts", "near one", (-8, 122), (-30, 124),
+                                  (70, 40), (110, -110), (-110, 110), (-100, 30), (20, -118)])
+@pytest.mark.parametrize("dims,ntv,R", [((3, 2, 2, 2), 3, 5), ((2, 3, 2, 1), 24, 40)])
+def test_multi_graded_operands(prec, kind, dims, ntv, R):
+    import numpy as np
+    import paper_2205_09104_amd as dc
+    from paper_2205_09104_amd import CoarseOp
+    V, n = dims[0] * dims[1] * dims[2] * dims[3], 2 * ntv
+    M, X = _graded(kind, prec, V, n, R, np.random.default_rng(ntv))
+    op = CoarseOp(torch.from_numpy(M[:, 0].copy()).cuda(), torch.from_numpy(M[:, 1:].copy()).cuda(),
+                  dims, store=("f64", prec))
+    nb = op.neighbours()
+    g = np.where(np.arange(n) < ntv, 1.0, -1.0)
+    for adj in (False, True):   # without a mass term D^H = Gamma5 D Gamma5
+        v = X * g if adj else X
+        ref = np.einsum("xij,rxj->rxi", M[:, 0], v)
+        mag = np.einsum("xij,rxj->rxi", abs(M[:, 0]), abs(v))
+        for mu in range(4):
+            f, b = nb[mu], nb[4 + mu]
+            ref += np.einsum("xij,rxj->rxi", M[:, 1 + mu], v[:, f])
+            mag += np.einsum("xij,rxj->rxi", abs(M[:, 1 + mu]), abs(v[:, f]))
+            ref += g * np.einsum("xji,rxj->rxi", M[b, 1 + mu].conj(), v[:, b] * g)
+            mag += np.einsum("xji,rxj->rxi", abs(M[b, 1 + mu]), abs(v[:, b]))
+        if adj:
+            ref = ref * g
+        # entries whose terms leave FP32's normal range in the sum are not compared
+        top, low = np.finfo(np.float32).max / 2, np.finfo(np.float32).tiny * 2.0 ** 24
+        use = (mag < top) & (mag > low)
+        assert use.any()
+        single = torch.stack([op.apply(torch.from_numpy(x.astype(np.complex64)).cuda(), prec=prec,
+                                       adjoint=adj) for x in X]).cpu().numpy()
+        es = np.max(np.where(use, abs(single - ref) / mag, 0))
+        for tile in (16, 32, 64):
+            try:
+                dc.set_multi_tile_mode(tile)
+                y = op.apply_multi(torch.from_numpy(X.astype(np.complex64)).cuda(), prec=prec,
+                                   adjoint=adj).cpu().numpy()
+            finally:
+                dc.set_multi_tile_mode(0)
+            err = np.where(use, abs(y - ref) / mag, 0)
+            log(f"  graded {kind} {prec} n {n} R {R} adjoint {adj} tile {tile}: "
+                f"{np.max(err):.1e} (single applies {es:.1e})")
+            assert np.max(err) <= 2e-6
+    op.close()
+
+
+# The multi-apply uses what the layout of the blocks recorded (largest entries, FP16
+# scales): after an update to blocks of very different size it must use the new ones.
+# Bound of the other comparisons with R single applies in the same storage.
+@pytest.mark.parametrize("factor", [1e4, 2.0 ** 80, 2.0 ** -90])
+def test_multi_after_update(factor):
+    from paper_2205_09104_amd import CoarseOp
+    import synth
+    dims, ntv, R = (3, 2, 4, 2), 6, 18
+    A, B = synth.self_blocks(dims, ntv, 3.0, 0).cuda(), synth.hop_blocks(dims, ntv, 0).cuda()
+    op = CoarseOp(A, B, dims, store=("f64", "f32", "f16s"))
+    V, n = A.shape[0], 2 * ntv
+    X = torch.stack([rand_vec(V, n, 41, r) for r in range(R)]).cuda().to(torch.complex64)
+    for _ in range(2):
+        for prec in ("f32", "f16s"):
+            ref = torch.stack([op.apply(x, prec=prec) for x in X])
+            y = op.apply_multi(X, prec=prec)
+            rel = float((y - ref).abs().to(torch.float64).div(ref.abs().max()).norm() /
+                        ref.abs().to(torch.float64).div(ref.abs().max()).norm())
+            assert rel <= 2e-6, (prec, factor, rel)
+        op.update(A * factor, B * factor)
+    op.close()
