@@ -799,8 +799,11 @@ constexpr int kFinishLds = 512;  // Hessenberg column length staged in LDS
 // Sec. 3.5): the coefficients come from one pass and h^2 = ||A v_j||^2 - sum |c1|^2;
 // a value at or below (brk ||A v_j||)^2 is a breakdown.  Two passes without nrm2: c2
 // carries ||w||^2 of the vector after the first pass, h^2 = ||w||^2 - sum |c2|^2.
-// The second pass's coefficients are rounding-sized against ||A v_j||, so the
-// difference keeps the precision of its terms, and the norm needs no pass of its own.
+// The difference is the norm of the final vector but for d sum |c2|^2, d the basis's
+// distance from orthonormality, and c2 itself is about d ||A v_j||: relative to h^2 at
+// most d (d / brk)^2 above the breakdown threshold.  Measured, recycle space included, d
+// is below 2e-7 in FP32 (brk 1e-6) and 4e-14 in FP64 (1e-14): below 1e-8 and 1e-12.  Where
+// h is larger the difference keeps the precision of its terms.
 struct StepNorm {
   double h;   // 0 for a breakdown
   bool breakdown;

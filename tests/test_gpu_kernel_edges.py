@@ -373,3 +373,48 @@ def test_multi_after_update(factor):
             assert rel <= 2e-6, (prec, factor, rel)
         op.update(A * factor, B * factor)
     op.close()
+
+
+# An Arnoldi step into a nearly invariant space: three eigenvalues and hops of size eps, so
+# the fourth vector's norm before scaling is rounding-sized against ||A v_j|| while the
+# breakdown threshold (1e-14, FP32 1e-6) is not reached; with no hops the space is invariant
+# and the process ends at three steps.  h_{43} against Arnoldi in extended precision; bound:
+# 50 units of rounding of ||A|| (64 entries, two passes over three vectors) over h.
+@pytest.mark.parametrize("prec,eps", [("f64", 1e-5), ("f64", 1e-9), ("f64", 1e-11),
+                                      ("f32", 1e-2), ("f32", 1e-3)])
+def test_arnoldi_nearly_invariant(prec, eps):
+    import numpy as np
+    from oracle import operator as dop
+    from paper_2205_09104_amd import CoarseOp, Opts
+    import synth
+    dims, ntv = (2, 2, 2, 2), 2
+    n, V = 4, 16
+    A = torch.zeros((V, n, n), dtype=torch.complex128)
+    for x in range(V):
+        for i in range(n):
+            A[x, i, i] = (1.0, 2.0, 4.0)[(x + i) % 3]
+    B = (synth.hop_blocks(dims, ntv, 0) * eps).to(torch.complex64).to(torch.complex128)
+    v = rand_vec(V, n, 43, 0).to(torch.complex64).to(torch.complex128)
+    for hops in (B, torch.zeros_like(B)):
+        op = CoarseOp(A.cuda(), hops.cuda(), dims, store=("f64", "f32"))
+        H, s = op.arnoldi(v.cuda(), 6, Opts(m=6, prec=prec))
+        op.close()
+        if hops is not B:
+            assert s == 3
+            continue
+        oop = dop.build(dims, A.numpy(), B.numpy(), 0.0)
+        D = np.stack([dop.apply(oop, e.reshape(V, n)).reshape(-1)
+                      for e in np.eye(V * n, dtype=np.complex128)], axis=1).astype(np.clongdouble)
+        q = [v.numpy().reshape(-1).astype(np.clongdouble)]
+        q[0] = q[0] / np.sqrt((abs(q[0]) ** 2).sum())
+        for j in range(3):
+            w = D @ q[j]
+            for _ in range(3):
+                for u in q:
+                    w = w - u * (u.conj() * w).sum()
+            h = np.sqrt((abs(w) ** 2).sum())
+            q.append(w / h)
+        unit = 2.0 ** (-52 if prec == "f64" else -23)
+        err = abs(float(H[3, 2].real) / float(h) - 1)
+        log(f"  nearly invariant {prec} eps {eps}: h {float(h):.3e}, relative error {err:.1e}")
+        assert s >= 4 and err <= 50 * unit * 4 / float(h)
