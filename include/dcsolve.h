@@ -452,7 +452,8 @@ int dc_profile_apply(dc_op_t op, int32_t every);
 
 /* Totals since the last dc_profile_apply for the blocks used in precision
  * prec (DC_PREC_F64 / DC_PREC_F32 / DC_PREC_F16S) and kernel 0 (the full
- * lattice's block kernel), 1 (the reduced operator's t_o = A_o^{-1} D_oe x_e
+ * lattice's block kernel; where blocks of at most 32 MB, FP64 with n <= 40, make the
+ * whole apply one launch, that launch), 1 (the reduced operator's t_o = A_o^{-1} D_oe x_e
  * kernel) or 2 (its A_e x_e - D_eo t_o kernel with the chain epilogue): *launches = launches that did work, *total_ms = their summed
  * event-to-event duration; *launches_all, *total_ms_all = the same over every
  * recorded launch, no-op launches of finished cycles included (what a kernel
@@ -464,8 +465,10 @@ int dc_profile_apply_read(dc_op_t op, int32_t prec, int32_t kernel, int64_t* lau
 /* Vector passes of the launches that dc_profile_apply_read counts as having
  * done work (same prec and kernel): per launch, the distinct vectors it reads
  * plus the vectors it writes, each spanning the kernel's rows (V for kernel 0,
- * V/2 for kernels 1 and 2).  Kernel 0: 1 (its input); kernel 1: 2 (x_e,
- * t_o); kernel 2: 2-5 by epilogue.  Together with the blocks a launch streams
+ * V/2 for kernels 1 and 2).  Kernel 0: 1 (its input), or 2 (input and output)
+ * where the apply is one launch, which also reads every hop block twice; kernel
+ * 1: 2 (x_e, t_o), or 9 (x_e and eight partial vectors) in the single-read form;
+ * kernel 2: 2-5 by epilogue, or 9-12.  Together with the blocks a launch streams
  * this gives the algorithmic bytes of the timed launches.  passes may be NULL. */
 int dc_profile_apply_passes(dc_op_t op, int32_t prec, int32_t kernel, int64_t* passes);
 

@@ -469,7 +469,8 @@ static void stage1(Op& op, Prec p, int n, int V, const void* blocks, const float
 }
 
 // out = D in (g5: Gamma5 D Gamma5 in), one_launch: in a single launch (in and out
-// must not overlap), timed in stage 1's slot, else stage 1 into gbuf and its gather.
+// must not overlap), timed in stage 1's slot as a launch that reads in and writes out,
+// else stage 1 into gbuf and its gather.
 static void apply_store(Op& op, Prec p, bool one_launch, const void* in, void* gbuf, void* out,
                         double tm, const int* done, hipStream_t st, int g5 = 0) {
   if (!one_launch) {
@@ -487,7 +488,7 @@ static void apply_store(Op& op, Prec p, bool one_launch, const void* in, void* g
   }
   launch_apply_site(p, op.n, op.V, op.blocks(p), op.scales(p), in, out, op.nbr.as<int>(), tm, done, st,
                     a, b, g5);
-  if (a) pr.recs.push_back({a, b, slot, done ? pr.tag : -1, false, 1});
+  if (a) pr.recs.push_back({a, b, slot, done ? pr.tag : -1, false, 2});   // in and out
 }
 
 // The reduced operator's kernels (Sec. 2.2, factored form), timed like stage1:

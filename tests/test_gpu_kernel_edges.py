@@ -418,3 +418,17 @@ def test_arnoldi_nearly_invariant(prec, eps):
         err = abs(float(H[3, 2].real) / float(h) - 1)
         log(f"  nearly invariant {prec} eps {eps}: h {float(h):.3e}, relative error {err:.1e}")
         assert s >= 4 and err <= 50 * unit * 4 / float(h)
+
+
+# The profile's kernel 0: a small operator's apply is one launch, which reads the input
+# and writes the output; a larger one's block kernel reads the input.
+def test_profile_passes_of_the_full_apply():
+    for dims, ntv, passes in (((4, 4, 4, 4), 8, 2), ((4, 4, 4, 4), 24, 1)):
+        gop, oop = make_pair(dims, ntv, 3.0)
+        x = rand_vec(oop.V, oop.n, 3, 0).cuda()
+        gop.profile_apply(1)
+        for adj in (False, True):
+            gop.apply(x, adjoint=adj)
+        assert gop.profile_apply_read("f64")[0] == 2
+        assert gop.profile_apply_passes("f64") == 2 * passes
+        gop.close()
