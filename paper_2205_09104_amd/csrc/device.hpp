@@ -15,11 +15,6 @@ __device__ inline T shfl_xor(T v, int m) {
 
 __device__ inline double gam(int i, int n) { return i < (n >> 1) ? 1.0 : -1.0; }
 
-template <typename R>
-__device__ inline cx<R> ld(const cx<R>* p) {
-  return *p;
-}
-
 // Block-wide sum of W doubles per thread (blockDim.x a multiple of 64, <= 1024),
 // written as this block's partial: partials[w * nblk + block].  A second
 // kernel (k_finalize) sums the partials of each value in a fixed order, so
@@ -89,7 +84,6 @@ __device__ inline int dpp_xor1(int v) { return __builtin_amdgcn_mov_dpp(v, 0xB1,
 __device__ inline int dpp_xor2(int v) { return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, false); }
 __device__ inline int dpp_hmirror(int v) { return __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, false); }
 __device__ inline int dpp_ror8(int v) { return __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, false); }
-
 
 // The two FP16 values of a packed 32-bit word, widened.
 __device__ inline float lo_h(uint32_t w) {

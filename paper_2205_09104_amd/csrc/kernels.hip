@@ -8,7 +8,6 @@
 #include <algorithm>
 #include <mutex>
 
-#include <hip/hip_fp16.h>
 
 // Scratch of the no-allocation reduced apply (dc_apply_reduced_noalloc): the
 // odd-row temporary t_o lives in this file-scope device array, one copy per
@@ -96,26 +95,11 @@ struct Tile<T, P32> {
   }
 };
 
-__device__ inline float h2f(uint32_t bits16) {
-  return __half2float(__ushort_as_half(static_cast<unsigned short>(bits16 & 0xffffu)));
-}
-
 template <int T>
 struct Tile<T, P16S> {
   using A = float;
   static constexpr int TT = T * T;
   static constexpr int UNITS = (TT + 3) / 4;
-  __device__ static void load(const void* base, int lane, cx<float> (&m)[TT]) {
-    const uint4* p = static_cast<const uint4*>(base);
-#pragma unroll
-    for (int u = 0; u < UNITS; ++u) {
-      const uint4 v = p[u * 64 + lane];
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (4 * u + q < TT) m[4 * u + q] = mk(h2f(w[q]), h2f(w[q] >> 16));
-    }
-  }
 };
 
 template <int P>
@@ -149,10 +133,6 @@ __device__ inline double dppd(double v) {
   return __longlong_as_double((long long)(unsigned(__float_as_int(lo))) |
                               ((long long)(__float_as_int(hi)) << 32));
 }
-__device__ inline float dpp_any(float v, int ctl) {
-  return ctl == 1 ? dppf<1>(v) : ctl == 2 ? dppf<2>(v) : ctl == 4 ? dppf<4>(v) : dppf<8>(v);
-}
-
 __device__ inline float sum_row8(float v) {  // over lc
   v += dppf<1>(v);
   v += dppf<2>(v);
