@@ -479,8 +479,10 @@ int dc_profile_apply_passes(dc_op_t op, int32_t prec, int32_t kernel, int64_t* p
  * fastest for the process.  dc_multi_tile returns the tile chosen for a shape
  * (0 if not tuned yet); dc_set_multi_tile_mode(0) returns to autotuning and
  * forgets the table, 16 / 32 / 64 forces that tile (FP64 uses 32 for 64);
- * other values are DC_ERR_INVALID.  Results do not depend on the tile (same arithmetic per
- * output entry). */
+ * other values are DC_ERR_INVALID.  FP64 results do not depend on the tile (same
+ * arithmetic per output entry); FP32 ones do, to rounding (the tile decides how the
+ * sums are shared between waves), so force a tile where a run must repeat another
+ * process bit for bit. */
 int dc_multi_tile(int32_t prec, int32_t n, int32_t n_rhs, int32_t sites);
 int dc_set_multi_tile_mode(int32_t mode);
 

@@ -14,13 +14,13 @@ namespace {
 
 // ------------------------------------------------------------------ multi-RHS apply
 // Y_r = D X_r for R right-hand sides at once: each of a site's nine couplings
-// times the n x R panel at its source.  One workgroup (4 waves) per site and
-// tile of RB right-hand sides, over a work list of the sites of up to
-// kMaxMultiOps operators (a mixed batch of lattices with one block size n);
-// grid.y tiles the right-hand sides of the operator with the most, tiles past
-// an operator's own count exit at entry.  Backward hops Gamma5 B^H Gamma5 use the
-// stored forward block transposed.  Every stored block is read once per site that uses it
-// (9 block reads per site).
+// times the n x R panel at its source.  A workgroup of 4 waves takes one site (two or
+// four where a small block leaves waves over) and a tile of RB right-hand sides, over a
+// work list of the sites of up to kMaxMultiOps operators (a mixed batch of lattices
+// with one block size n); grid.y tiles the right-hand sides of the operator with the
+// most, tiles past an operator's own count do nothing.  Backward hops Gamma5 B^H Gamma5
+// use the stored forward block transposed.  Every stored block is read once per site
+// that uses it (9 block reads per site).
 
 typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 typedef __bf16 b2 __attribute__((ext_vector_type(2)));
@@ -315,13 +315,13 @@ __global__ __launch_bounds__(256, T <= 6 ? 2 : 1) void k_apply_multi_f64(MultiOp
 // more, entries below 2^-110 are held to 2^-133.
 // Layout: complex values stay interleaved, (re, im) pairs are two k entries:
 // Re = (ar, ai) . (pr, -pi), Im = (ar, ai) . (pi, pr), on 16x16x32 tiles (16
-// complex columns per step).  One workgroup per site and RB right-hand sides:
-// its four waves take the RB / 16 column tiles, and the row tiles where there
-// are fewer.  The couplings' blocks go through LDS as BF16 pairs, a plane per piece
-// (rows padded to an odd number of 16-byte units: conflict-free fragment reads); the panels go from memory to the wave
-// that multiplies them, which holds its fragments in registers and splits them one
-// k step at a time, between the products.  A step's products are summed small ones
-// first, from zero, and then added.
+// complex columns per step).  The four waves of a workgroup take the RB / 16 column
+// tiles, and share the k steps of each where there are fewer.  The couplings' blocks
+// go through LDS as BF16 pairs, a plane per piece (rows padded to an odd number of
+// 16-byte units: conflict-free fragment reads); the panels go from memory to the wave
+// that multiplies them, which holds its fragments in registers and splits them one k
+// step at a time, between the products.  A step's products are summed small ones first,
+// from zero, and then added.
 // Measured (16^4, n = 48, 64 right-hand sides; FP32 matrix instructions, three real products
 // per complex one, and planes in LDS before): FP32 6.70 -> 5.18 ms, FP16 blocks 6.87 -> 4.14
 // ms; 12 right-hand sides: 2.29 -> 2.21 and 2.38 -> 1.61 ms.  At 64 in FP32, matrix cores 44%,
