@@ -503,6 +503,14 @@ __device__ __forceinline__ const uint4* block_ptr(const void* blocks, size_t ite
   return static_cast<const uint4*>(blocks) + item * (size_t(Tile<T, P>::UNITS) * 64);
 }
 
+// Tile `item` into R; non-temporally if `stream` says so, FP16 tiles always.
+template <int T, int P>
+__device__ __forceinline__ void load_block_tile(TileRegs<T, P>& R, const void* blocks, size_t item,
+                                                int lane, int stream) {
+  if (P == P16S || stream) R.load_stream(block_ptr<T, P>(blocks, item), lane);
+  else R.load(block_ptr<T, P>(blocks, item), lane);
+}
+
 // The full-lattice apply in one launch, for operators whose blocks stay in the caches:
 // workgroup per site, wave 0 the self block, waves 1-4 the forward hops, 5-8 the
 // backward hops, summed in the order of the two-kernel form (equal bit for bit).
@@ -808,8 +816,9 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduced_eo(
 // of eighteen; the sums and signs are those of the two-kernel form, so the
 // results agree with it bit for bit.
 //
-// Eight waves per workgroup, one per hop tile; the tiles and the inverse are
-// loaded non-temporally (one launch reads each once).  The odd site's inverse tile is
+// Eight waves per workgroup, one per hop tile; the inverse, and the tiles of operators
+// beyond the last-level cache (FP16 ones of any), are loaded non-temporally (one
+// launch reads each once).  The odd site's inverse tile is
 // staged in LDS and its product with the summed hop products is split over the
 // eight waves: wave w takes rows w T .. w T + T - 1, which lane group lr = w
 // holds in the one-wave tile layout; its lane (a, lc) forms the partial sum
@@ -825,7 +834,7 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduced_eo(
 template <int T, int P>
 constexpr int scatter_min_waves() { return (P == P16S && T <= 6) ? 7 : 1; }
 
-template <int T, int P, bool FULL, bool G5>
+template <int T, int P, bool FULL, bool G5, bool NT>
 __global__ __launch_bounds__(512, (scatter_min_waves<T, P>())) void k_reduced_scatter(
     const void* __restrict__ blocks, const float* __restrict__ scales,
     const void* __restrict__ inv, const float* __restrict__ invsc,
@@ -858,7 +867,7 @@ __global__ __launch_bounds__(512, (scatter_min_waves<T, P>())) void k_reduced_sc
   size_t dst = 0;   // element offset of this wave's D_eo product in hp
   if (w < 4) {
     const int item = 5 * x + 1 + w;
-    R.load_stream(block_ptr<T, P>(blocks, size_t(item)), lane);
+    load_block_tile<T, P>(R, blocks, size_t(item), lane, NT);
     if (P == P16S) s = A(scales[item]);
     const int src = nbr[w * V + x];
     wave_product<T, P, FULL, 1>(R, s, x_e + size_t(src >> 1) * n, part[w], n, 0.0, lane, G5 ? 1 : 0);
@@ -867,7 +876,7 @@ __global__ __launch_bounds__(512, (scatter_min_waves<T, P>())) void k_reduced_sc
     const int mu = w - 4;
     const int y = nbr[(4 + mu) * V + x];
     const int item = 5 * y + 1 + mu;
-    R.load_stream(block_ptr<T, P>(blocks, size_t(item)), lane);
+    load_block_tile<T, P>(R, blocks, size_t(item), lane, NT);
     if (P == P16S) s = A(scales[item]);
     wave_product<T, P, FULL, 2>(R, s, x_e + size_t(y >> 1) * n, part[w], n, 0.0, lane, G5 ? 1 : 0);
     dst = (size_t(y >> 1) * 8 + mu) * n;             // forward hop mu of even x - mu
@@ -944,7 +953,7 @@ __global__ __launch_bounds__(64) void k_reduced_gather(
     const cx<typename VecOf<P>::R>* x_e, const cx<typename VecOf<P>::R>* __restrict__ hp,
     const int* __restrict__ esite, int V, int n, int chunk, double tm,
     cx<typename VecOf<P>::R>* out, const cx<typename VecOf<P>::R>* e, cx<typename VecOf<P>::R>* y,
-    z64 c0, z64 ca, z64 cb, const int* __restrict__ done) {
+    z64 c0, z64 ca, z64 cb, int stream, const int* __restrict__ done) {
   using A = typename Tile<T, P>::A;
   using VR = typename VecOf<P>::R;
   __shared__ cx<VR> self_part[64];
@@ -956,7 +965,7 @@ __global__ __launch_bounds__(64) void k_reduced_gather(
   const int x = esite[r];
   const int lane = threadIdx.x;
   TileRegs<T, P> R;
-  if (BJ) R.load_stream(block_ptr<T, P>(einv, size_t(x)), lane);
+  if (BJ) load_block_tile<T, P>(R, einv, size_t(x), lane, stream);
   cx<VR> h[8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
@@ -1008,7 +1017,7 @@ __global__ __launch_bounds__(64) void k_reduced_gather(
   } else {
     if (x_e) {
       const int item = 5 * x;
-      R.load_stream(block_ptr<T, P>(blocks, size_t(item)), lane);
+      load_block_tile<T, P>(R, blocks, size_t(item), lane, stream);
       const A s = (P == P16S) ? A(scales[item]) : A(1);
       wave_product<T, P, FULL, 0>(R, s, x_e + size_t(r) * n, self_part, n, tm, lane, G5 ? 1 : 0);
     } else {
@@ -1613,9 +1622,27 @@ static bool single_read_fits(Prec p, int n) {
 // 47 MB 14.1 / 12.6; one apply at 12^4, n = 48 (3.8 GB): 1179 / 752 us.
 constexpr size_t kSingleReadF64Bytes = size_t(24) << 20;
 
+// FP32 and FP64 tiles are loaded non-temporally where the blocks of an apply do not fit
+// the 256 MB last-level cache (a pass leaves enough of them there up to somewhat more).
+// Cached / non-temporal, one apply, us: FP32 51 MB n = 8 32.7 / 35.6, 202 MB n = 16 41.9 /
+// 49.4, 270 MB n = 16 59.3 / 65.7, 304 MB n = 24 67.1 / 65.6, 506 MB n = 48 99.9 / 93.2; FP64
+// 135 MB n = 8 44.0 / 50.0, 270 MB n = 24 48.8 / 52.9, 405 MB n = 24 85.4 / 78.5.  FP16 tiles
+// always are: cached they gained between 100 and 200 MB only (190 MB, n = 48: 36.5 / 38.1)
+// and lost on either side (60 MB 19.7 / 16.8, 430 MB 90.6 / 81.7).
+static int reduced_stream(int p, int n, int V) {
+  const size_t edge = size_t(tile_T(n)) * 8;
+  return size_t(V) * 5 * edge * edge * block_entry(p) > kCacheBytes + kCacheBytes / 8;
+}
+
 bool reduced_single_read(Prec p, int n, int V) {
   if (g_reduced_mode == 1 || !single_read_fits(p, n)) return false;
   return p != P64 || size_t(V) * 5 * n * n * sizeof(z64) > kSingleReadF64Bytes;
+}
+
+template <int T, int P, bool FULL, bool G5>
+static auto scatter_kernel(int stream) {
+  if constexpr (P == P16S) return k_reduced_scatter<T, P, FULL, G5, true>;
+  else return stream ? k_reduced_scatter<T, P, FULL, G5, true> : k_reduced_scatter<T, P, FULL, G5, false>;
 }
 
 template <int P>
@@ -1630,13 +1657,14 @@ static void reduced_scatter_T(int n, int V, const void* blocks, const float* sca
   const auto* xe = static_cast<const cx<VR>*>(x_e);
   auto* h = static_cast<cx<VR>*>(hp);
   const bool full = (n % 8) == 0;
+  const int stream = reduced_stream(P, n, V);
   switch (tile_T(n)) {
 #define DC_CASE(TV)                                                                                    \
   case TV:                                                                                             \
     if constexpr (single_read_tile<P>(TV)) {                                                           \
       const auto k =                                                                                   \
-          full ? (g5 ? k_reduced_scatter<TV, P, true, true> : k_reduced_scatter<TV, P, true, false>)   \
-               : (g5 ? k_reduced_scatter<TV, P, false, true> : k_reduced_scatter<TV, P, false, false>);\
+          full ? (g5 ? scatter_kernel<TV, P, true, true>(stream) : scatter_kernel<TV, P, true, false>(stream))   \
+               : (g5 ? scatter_kernel<TV, P, false, true>(stream) : scatter_kernel<TV, P, false, false>(stream));\
       hipExtLaunchKernelGGL(k, grid, block, 0, st, ev0, ev1, 0, blocks, scales, inv, invsc, xe,        \
                             h, nbr, osite, V, n, chunk, done);                                         \
     }                                                                                                  \
@@ -1680,6 +1708,7 @@ static void reduced_gather_T(int n, int V, const void* blocks, const float* scal
   auto* yy = static_cast<cx<VR>*>(y);
   const bool full = (n % 8) == 0;
   constexpr bool E0 = EPI == 0;   // Gamma5 comes with the plain store only
+  const int stream = reduced_stream(P, n, V);
   switch (tile_T(n)) {
 #define DC_CASE(TV)                                                                       \
   case TV:                                                                                \
@@ -1690,7 +1719,7 @@ static void reduced_gather_T(int n, int V, const void* blocks, const float* scal
                                       : k_reduced_gather<TV, P, false, EPI, BJ, false>);  \
       hipExtLaunchKernelGGL(k, grid, block, 0, st, ev0, ev1, 0, blocks, scales, einv,     \
                             einvsc, xe, h, esite, V, n, chunk, tm, o, ee, yy,             \
-                            c0, ca, cb, done);                                            \
+                            c0, ca, cb, stream, done);                                    \
     }                                                                                     \
     break;
     DC_CASE(1) DC_CASE(2) DC_CASE(3) DC_CASE(4) DC_CASE(5) DC_CASE(6) DC_CASE(7) DC_CASE(8)

@@ -432,3 +432,36 @@ def test_profile_passes_of_the_full_apply():
         assert gop.profile_apply_read("f64")[0] == 2
         assert gop.profile_apply_passes("f64") == 2 * passes
         gop.close()
+
+
+# Single-read form around the size from which its tiles are loaded non-temporally (288 MB
+# of blocks), full and ragged tiles: bit for bit the two-kernel form, forward, adjoint and
+# with block Jacobi.
+@pytest.mark.parametrize("dims,ntv,prec", [((4, 8, 6, 6), 24, "f64"), ((8, 8, 6, 6), 24, "f64"),
+                                           ((8, 8, 6, 6), 21, "f64"), ((8, 8, 6, 6), 24, "f32"),
+                                           ((8, 8, 8, 8), 24, "f32"), ((8, 8, 8, 8), 21, "f32")])
+def test_single_read_around_the_cache_size(dims, ntv, prec):
+    import paper_2205_09104_amd as dc
+    from paper_2205_09104_amd import CoarseOp
+    V, n = dims[0] * dims[1] * dims[2] * dims[3], 2 * ntv
+    g = torch.Generator(device="cuda").manual_seed(5)
+
+    def rand(*shape):
+        return torch.randn(*shape, dtype=torch.complex128, device="cuda", generator=g)
+
+    A = rand(V, n, n) * 0.3 / n ** 0.5 + 4.0 * torch.eye(n, dtype=torch.complex128, device="cuda")
+    op = CoarseOp(A, rand(V, 4, n, n) / n ** 0.5, dims, mu=0.1, store=("f64", prec))
+    del A
+    x = rand(V // 2, n).to(torch.complex128 if prec == "f64" else torch.complex64)
+    for kw in (dict(), dict(adjoint=True), dict(block_jacobi=True)):
+        try:
+            dc.set_reduced_kernels(1)
+            a = op.apply_reduced(x, prec=prec, **kw)
+        finally:
+            dc.set_reduced_kernels(0)
+        op.profile_apply(1)
+        b = op.apply_reduced(x, prec=prec, **kw)
+        assert op.profile_apply_passes(prec, 1) == 9
+        op.profile_apply(0)
+        assert torch.equal(a, b) and bool(torch.isfinite(b.abs()).all())
+    op.close()
