@@ -452,8 +452,8 @@ int dc_profile_apply(dc_op_t op, int32_t every);
 
 /* Totals since the last dc_profile_apply for the blocks used in precision
  * prec (DC_PREC_F64 / DC_PREC_F32 / DC_PREC_F16S) and kernel 0 (the full
- * lattice's block kernel; where blocks of at most 32 MB, FP64 with n <= 40, make the
- * whole apply one launch, that launch), 1 (the reduced operator's t_o = A_o^{-1} D_oe x_e
+ * lattice's block kernel; where at most 4,096 sites with at most 32 MB of tiled blocks,
+ * FP64 with n <= 40, make the whole apply one launch, that launch), 1 (the reduced operator's t_o = A_o^{-1} D_oe x_e
  * kernel) or 2 (its A_e x_e - D_eo t_o kernel with the chain epilogue): *launches = launches that did work, *total_ms = their summed
  * event-to-event duration; *launches_all, *total_ms_all = the same over every
  * recorded launch, no-op launches of finished cycles included (what a kernel

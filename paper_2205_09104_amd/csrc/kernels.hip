@@ -1361,19 +1361,24 @@ void launch_apply_blocks(Prec p, int n, int V, const void* blocks, const float* 
   else apply_T<P16S>(n, V, blocks, scales, in, gbuf, nbr, tm, done, st, ev0, ev1, g5);
 }
 
-// The one-launch form reads every hop block twice: it is the faster one while that
-// costs less than a second launch and the slots' way through the caches, so up to
-// the eight 4 MB L2s (one apply, two launches / one, us): 5 MB FP64 11.1 / 8.6, 20 MB
-// FP16 11.1 / 8.7, 28 MB FP32 11.0 / 8.5; 40 MB FP64 11.7 / 12.4, 57 MB FP64 14.0 / 15.4.
+// The one-launch form reads every hop block twice and takes nine waves a site: it is the
+// faster one while that costs less than a second launch and the slots' way through the
+// caches, so up to the eight 4 MB L2s of tiled blocks (one apply, two launches / one, us):
+// 5 MB FP64 11.1 / 8.6, 20 MB FP16 11.1 / 8.7, 28 MB FP32 11.0 / 8.5; 40 MB FP64 11.7 / 12.4, 42
+// MB FP64 n = 12 (22 MB of entries) 11.7 / 13.7; and up to 16 workgroups per CU, beyond
+// which their number is what it waits for: 4,096 sites FP64 n = 8 11.2 / 10.4, FP32 n = 8
+// 11.0 / 8.7; 6,144 sites 12.4 / 18.2 and 11.4 / 11.6, 16,384 sites n = 2 22 / 46 and 22 / 28.
 constexpr size_t kSiteBytes = size_t(32) << 20;
+constexpr int kSiteMax = 4096;
 
 // Tiles it takes: FP64 tiles of T >= 6 would spill (nine waves: 168 registers each).
 template <int P>
 constexpr bool site_tile(int T) { return T >= 1 && T <= (P == P64 ? 5 : 8); }
 
 bool apply_one_launch(Prec p, int n, int V) {
-  if (p == P64 && !site_tile<P64>(tile_T(n))) return false;
-  return size_t(V) * 5 * n * n * block_entry(p) <= kSiteBytes;
+  if ((p == P64 && !site_tile<P64>(tile_T(n))) || V > kSiteMax) return false;
+  const size_t edge = size_t(tile_T(n)) * 8;
+  return size_t(V) * 5 * edge * edge * block_entry(p) <= kSiteBytes;
 }
 
 template <int P>

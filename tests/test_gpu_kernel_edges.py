@@ -465,3 +465,26 @@ def test_single_read_around_the_cache_size(dims, ntv, prec):
         op.profile_apply(0)
         assert torch.equal(a, b) and bool(torch.isfinite(b.abs()).all())
     op.close()
+
+
+# Which operators' full apply is one launch (two vector passes in the profile, one with
+# two launches): up to 4,096 sites, beyond which its workgroups cost more than the second
+# launch, and up to 32 MB of blocks as they are stored, padded to whole tiles.
+@pytest.mark.parametrize("dims,ntv,prec,passes", [
+    ((8, 8, 8, 8), 3, "f64", 2), ((8, 8, 13, 5), 3, "f64", 1), ((8, 8, 13, 5), 3, "f16s", 1),
+    ((9, 7, 5, 13), 3, "f32", 2), ((16, 8, 8, 8), 1, "f32", 1), ((8, 8, 8, 4), 5, "f64", 1),
+    ((8, 8, 8, 3), 5, "f64", 2), ((8, 8, 8, 4), 8, "f32", 2), ((8, 8, 8, 7), 8, "f32", 1)])
+def test_one_launch_apply_range(dims, ntv, prec, passes):
+    from paper_2205_09104_amd import CoarseOp
+    V, n = dims[0] * dims[1] * dims[2] * dims[3], 2 * ntv
+    g = torch.Generator(device="cuda").manual_seed(5)
+    A = torch.randn(V, n, n, dtype=torch.complex128, device="cuda", generator=g)
+    B = torch.randn(V, 4, n, n, dtype=torch.complex128, device="cuda", generator=g)
+    op = CoarseOp(A, B, dims, store=("f64", prec))
+    x = torch.randn(V, n, dtype=torch.complex128, device="cuda", generator=g)
+    y = op.apply(x)
+    op.profile_apply(1)
+    z = op.apply(x if prec == "f64" else x.to(torch.complex64), prec=prec)
+    assert op.profile_apply_read(prec)[0] == 1 and op.profile_apply_passes(prec) == passes
+    assert _rel(z.to(torch.complex128), y) <= {"f64": 0.0, "f32": 2e-6, "f16s": 3e-3}[prec]
+    op.close()
