@@ -1321,7 +1321,9 @@ constexpr size_t block_entry(int p) { return p == P64 ? 16 : p == P32 ? 8 : 4; }
 // slots.  Within it a repeated apply finds them there, unless the loads say that
 // they are not reused (one apply, cached / non-temporal, us; n = 48 but for the first):
 // 80 MB FP64 n = 16 18.9 / 21.1, 180 MB FP16 36.2 / 42.5, 360 MB FP32 78.5 / 68.4,
-// 720 MB FP64 157 / 141, 2.9 GB FP16 659 / 626, 5.8 GB FP32 1202 / 1084.
+// 720 MB FP64 157 / 141, 2.9 GB FP16 659 / 626, 5.8 GB FP32 1202 / 1084.  At 270 MB what a pass
+// leaves there still helps FP64 (n = 24 53.5 / 57.1, n = 16 57.0 / 59.3), not FP32 (n = 16 64.1 /
+// 60.7) or FP16 (n = 32 63.2 / 61.8): FP64's line is 288 MB.
 constexpr size_t kCacheBytes = size_t(256) << 20;
 
 template <int P>
@@ -1333,7 +1335,8 @@ static void apply_T(int n, int V, const void* blocks, const float* scales, const
   const dim3 grid(unsigned(chunk) * 8u), block(64);
   const auto* pin = static_cast<const cx<VR>*>(in);
   auto* pg = static_cast<cx<VR>*>(gbuf);
-  const int stream = size_t(V) * 5 * n * n * block_entry(P) > kCacheBytes;
+  const size_t fits = P == P64 ? kCacheBytes + kCacheBytes / 8 : kCacheBytes;
+  const int stream = size_t(V) * 5 * n * n * block_entry(P) > fits;
   const bool full = (n % 8) == 0;
   switch (tile_T(n)) {
   // with events: the dispatch itself records its start and end (no marker packets)
