@@ -1268,36 +1268,45 @@ __global__ void k_oddeven_split(int n, int H, const int* __restrict__ esite,
 
 // ------------------------------------------------------------------ gradient
 // d S / d B[x, dir]: the n x n outer products of a site and its neighbour, bound by the
-// writes.  A thread keeps column j for every 256 / n rows, so its neighbour entries are
-// read once and nothing is divided in the loop.  8^4, n = 32, tied (268 MB): 50.6 us
-// with a division per entry, 48.3 now, 5.6 TB/s (non-temporal stores: 51).
+// writes.  Thread (i, j), i < rows = min(256 / n, n), keeps column j for every rows-th row,
+// so its neighbour entries are read once and nothing is divided in the loop; threads
+// past the rows end at once.  inv = 65536 / n + 1 divides a thread number by n exactly.
+// Measured, us, with a division per entry / now: 8^4 tied n = 32 (268 MB) 50.6 / 48.3
+// in the kernel (5.6 TB/s; non-temporal stores: 51); calls of 1,800 sites tied n = 20 12.0 /
+// 10.8, n = 26 17.1 / 15.0, 4,096 sites untied n = 10 13.7 / 14.0 (18.0 with threads past the rows
+// loading, and the rows' entries loaded after the neighbour's).
 __global__ __launch_bounds__(256) void k_grad_hops(const z64* __restrict__ lam,
                                                    const z64* __restrict__ x,
                                                    z64* __restrict__ grad,
                                                    const int* __restrict__ nbr, int V, int n,
-                                                   int tied) {
+                                                   int tied, int rows, unsigned inv) {
   typedef double d2 __attribute__((ext_vector_type(2)));
   const int site = blockIdx.x;
   const int dir = blockIdx.y;  // 0..7 untied, 0..3 tied
-  const int rows = 256 / n;    // n <= 64
-  const int i0 = int(threadIdx.x) / n, j = int(threadIdx.x) - i0 * n;
+  const int i0 = int(threadIdx.x * inv) >> 16, j = int(threadIdx.x) - i0 * n;
   if (i0 >= rows) return;
+  // the rows' own entries are loaded a row ahead, the first ones beside the neighbour's
+  const z64 *ls = lam + size_t(site) * n, *xs = x + size_t(site) * n;
+  z64 l = ls[i0], xx = tied ? xs[i0] : mk(0.0, 0.0);
   const int y = nbr[dir * V + site];
   d2* out = reinterpret_cast<d2*>(grad) + (size_t(site) * (tied ? 4 : 8) + dir) * (size_t(n) * n) + j;
   const z64 xv = x[size_t(y) * n + j];
   const z64 ly = tied ? lam[size_t(y) * n + j] : mk(0.0, 0.0);
   const double gj = gam(j, n);
   for (int i = i0; i < n; i += rows) {
-    const z64 l = lam[size_t(site) * n + i];
+    const z64 li = l, xi = xx;
+    if (i + rows < n) {
+      l = ls[i + rows];
+      if (tied) xx = xs[i + rows];
+    }
     // -lambda_x,i * conj(x_y,j)
-    double gr = -(l.re * xv.re + l.im * xv.im);
-    double gi = -(l.im * xv.re - l.re * xv.im);
+    double gr = -(li.re * xv.re + li.im * xv.im);
+    double gi = -(li.im * xv.re - li.re * xv.im);
     if (tied) {
       // - g5_i x_x,i conj(lambda_y,j) g5_j
-      const z64 xx = x[size_t(site) * n + i];
       const double s = gam(i, n) * gj;
-      gr -= s * (xx.re * ly.re + xx.im * ly.im);
-      gi -= s * (xx.im * ly.re - xx.re * ly.im);
+      gr -= s * (xi.re * ly.re + xi.im * ly.im);
+      gi -= s * (xi.im * ly.re - xi.re * ly.im);
     }
     out[size_t(i) * n] = d2{gr, gi};
   }
@@ -1908,7 +1917,7 @@ void launch_gather_resid(Prec p, int n, int V, const void* gbuf, const void* b, 
 void launch_grad_hops(const z64* lam, const z64* x, z64* grad, const int* nbr, int V, int n,
                       int tied, hipStream_t st) {
   hipLaunchKernelGGL(k_grad_hops, dim3(unsigned(V), tied ? 4u : 8u), dim3(256), 0, st, lam, x,
-                     grad, nbr, V, n, tied);
+                     grad, nbr, V, n, tied, std::min(256 / n, n), 65536u / unsigned(n) + 1u);
   DC_HIP(hipGetLastError());
 }
 

@@ -488,3 +488,26 @@ def test_one_launch_apply_range(dims, ntv, prec, passes):
     assert op.profile_apply_read(prec)[0] == 1 and op.profile_apply_passes(prec) == passes
     assert _rel(z.to(torch.complex128), y) <= {"f64": 0.0, "f32": 2e-6, "f16s": 3e-3}[prec]
     op.close()
+
+
+# The hop gradient's thread mapping: one row and many rows per pass, threads past the rows
+# (n < 16), rows that do not divide n, the largest n, extents of one site.  Two or four
+# products per entry: rounding only, 1e-14 of the largest.
+@pytest.mark.parametrize("dims,ntv", [((3, 2, 1, 2), 1), ((2, 3, 2, 2), 3), ((2, 2, 2, 2), 7),
+                                      ((2, 1, 3, 2), 8), ((2, 2, 2, 1), 9), ((1, 2, 2, 2), 16),
+                                      ((2, 2, 1, 2), 21), ((2, 2, 2, 1), 32)])
+def test_grad_hops_thread_mapping(dims, ntv):
+    gop, oop = make_pair(dims, ntv, 3.0)
+    V, n = oop.V, oop.n
+    lam, x = rand_vec(V, n, 61, 0).cuda(), rand_vec(V, n, 61, 1).cuda()
+    nb = torch.from_numpy(gop.neighbours()).long().cuda()
+    g5 = torch.where(torch.arange(n, device="cuda") < ntv, 1.0, -1.0).to(torch.complex128)
+    for tied in (True, False):
+        out = gop.grad_hops(lam, x, tied=tied)
+        for d in range(4 if tied else 8):
+            y = nb[d]
+            ref = -lam[:, :, None] * x[y].conj()[:, None, :]
+            if tied:
+                ref = ref - (g5 * x)[:, :, None] * (lam[y].conj() * g5)[:, None, :]
+            assert float((out[:, d] - ref).abs().max()) <= 1e-14 * float(ref.abs().max())
+    gop.close()
