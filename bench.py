@@ -330,9 +330,9 @@ def main():
     if a.multi_rhs > 0:
         R = a.multi_rhs
         flops = 72.0 * V * n * n * R           # complex n x n times n x R per coupling, 9 couplings
-        # FP32 vectors run as FP16 pieces: three FP16 products (2,516 TFLOP/s dense) per
-        # product with FP32 blocks, two with FP16 blocks
-        for p, peak in (("f64", 78.6), ("f32", 838.7), ("f16s", 1258.0)):
+        # FP32 vectors run as BF16 pieces: six BF16 products (2,516 TFLOP/s dense) per
+        # product with FP32 blocks, five with FP16 blocks
+        for p, peak in (("f64", 78.6), ("f32", 419.3), ("f16s", 503.2)):
             X = torch.stack([synth.rhs(w.dims, w.n_tv, 500 + r, device="cuda") for r in range(R)])
             X = X if p == "f64" else X.to(torch.complex64)
             Y = torch.empty_like(X)
@@ -350,7 +350,7 @@ def main():
             ms = sorted(times)[2]
             tf = flops / (ms * 1e-3) / 1e12
             multi[p] = {"n_rhs": R, "ms": ms, "TFLOP/s": tf, "peak": peak, "frac": tf / peak,
-                        "mfma": "f64 16x16x4" if p == "f64" else "f16 16x16x32 pieces"}
+                        "mfma": "f64 16x16x4" if p == "f64" else "bf16 16x16x32 pieces"}
             log(f"multi-RHS apply {p} R={R}: {ms:.3f} ms, {tf:.1f} TFLOP/s ({100 * tf / peak:.1f}% of {peak})")
             del X, Y
 

@@ -93,7 +93,7 @@ __device__ inline MultiOpDesc op_of(const MultiOps& ops, unsigned item) {
 // added in LDS at the end, in wave order whatever the tile, so results do not
 // depend on RB.
 // Measured (FP64; before: planes staged through registers, three of four waves
-// multiplying): 8^4, n = 48, 12 right-hand sides 412 -> 261 us, 16^4, 64: 25.7 -> 14.2
+// multiplying): 8^4, n = 48, 12 right-hand sides 412 -> 237 us, 16^4, 64: 25.7 -> 14.2
 // ms, 8^4, n = 16, 32: 84 -> 67 us.  Matrix cores 46% busy at 12 right-hand sides;
 // operands loaded straight from the tiled block to registers cost one address
 // per lane and ran at 312 us.

@@ -142,7 +142,7 @@ __global__ __launch_bounds__(256) void k_layout(const z64* __restrict__ self_in,
 // Bound by instruction issue (about 450 per column, 4 T^2 of them FMAs) at two
 // waves per SIMD.  8^4, n = 48, FP64 and FP16 outputs: 990 us (matrix in LDS,
 // four waves and barriers per column, bound by LDS passes) -> 340 us (registers
-// of four waves, two barriers) -> 260 us.
+// of four waves, two barriers) -> 279-286 us.
 template <int T>
 __global__ __launch_bounds__(64) void k_invert_blocks(const z64* __restrict__ tiled64, int n,
                                                       double tm, z64* o64, z32* o32,
