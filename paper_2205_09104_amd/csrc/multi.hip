@@ -604,8 +604,9 @@ __global__ __launch_bounds__(256, (SplitShape<T, P, RB>::WAVES)) void k_apply_mu
       else store_block(nb, scale_of(c + 1), true);
       if (c + 2 < 9) load_block(block_of(c + 2));
     }
-    // both factors undone in one: what would overflow here overflows in the result
-    const float f = fminf(fblk * down, FLT_MAX);
+    // both factors undone in one: what would overflow here overflows in the result (a
+    // scale that is not finite stays so)
+    const float f = fblk <= FLT_MAX ? fminf(fblk * down, FLT_MAX) : fblk;
 #pragma unroll
     for (int t = 0; t < KSW; ++t) {
       if (KS % KG != 0 && kg + KG * t >= KS) continue;

@@ -511,3 +511,29 @@ def test_grad_hops_thread_mapping(dims, ntv):
                 ref = ref - (g5 * x)[:, :, None] * (lam[y].conj() * g5)[:, None, :]
             assert float((out[:, d] - ref).abs().max()) <= 1e-14 * float(ref.abs().max())
     gop.close()
+
+
+# Blocks with entries beyond FP32, infinite or NaN in reduced storage: the multi-apply is
+# finite where the single apply is, and nowhere else.
+@pytest.mark.parametrize("prec", ["f32", "f16s"])
+@pytest.mark.parametrize("bad", [1e39, float("inf"), float("nan")])
+def test_multi_nonfinite_blocks(prec, bad):
+    from paper_2205_09104_amd import CoarseOp
+    import synth
+    dims, ntv, R = (4, 3, 2, 2), 5, 9
+    A, B = synth.self_blocks(dims, ntv, 3.0, 0), synth.hop_blocks(dims, ntv, 0)
+    A[7, 3, 2] = bad
+    B[20, 1, 4, 4] = bad
+    op = CoarseOp(A.cuda(), B.cuda(), dims, store=("f64", prec))
+    V, n = A.shape[0], 2 * ntv
+    X = torch.stack([rand_vec(V, n, 47, r) for r in range(R)]).cuda().to(torch.complex64)
+    ref = torch.stack([op.apply(x, prec=prec) for x in X])
+    y = op.apply_multi(X, prec=prec)
+    want = torch.isfinite(torch.view_as_real(ref)).all(-1)
+    have = torch.isfinite(torch.view_as_real(y)).all(-1)
+    assert not bool(want[:, 7, 3].any())                 # the row of the bad entry
+    assert torch.equal(want.all(-1), have.all(-1))       # the same sites
+    assert not bool((have & ~want).any())                # no entry turned finite
+    keep = want.all(-1)
+    assert float((y[keep] - ref[keep]).abs().max()) <= 2e-6 * float(ref[keep].abs().max())
+    op.close()
